@@ -146,6 +146,111 @@ def work(case):
     return {"bytes": rows * d * size + codes + 2 * rows * N, "flops": 2 * rows * d_e * N + rows * d_e * k}
 
 
+def _sylvester(n):
+    H = torch.ones((1, 1), dtype=torch.float64, device="cuda")
+    while H.shape[0] < n:
+        H = torch.cat((torch.cat((H, H), 1), torch.cat((H, -H), 1)), 0)
+    return H
+
+
+def _paley(b):
+    """I + [[0, 1], [-1, Q]] with Q[i][j] the quadratic character of i - j over GF(b - 1), b - 1 prime or 7^3 (polynomials
+    over GF(7) modulo t^3 + t + 1, element number c0 + 7 c1 + 49 c2)."""
+    if b == 1:
+        return torch.ones((1, 1), dtype=torch.float64, device="cuda")
+    q = b - 1
+    i = torch.arange(q)
+    if q == 343:
+        digits = torch.stack((i % 7, i // 7 % 7, i // 49), 1)
+        a0, a1, a2 = digits.unbind(1)
+        p = [a0 * a0, 2 * a0 * a1, 2 * a0 * a2 + a1 * a1, 2 * a1 * a2, a2 * a2]
+        p[2], p[1] = p[2] - p[4], p[1] - p[4]                # t^4 = -t^2 - t
+        p[1], p[0] = p[1] - p[3], p[0] - p[3]                # t^3 = -t - 1
+        square = p[0] % 7 + 7 * (p[1] % 7) + 49 * (p[2] % 7)
+        minus = (digits[:, None] - digits[None]) % 7
+        minus = minus[..., 0] + 7 * minus[..., 1] + 49 * minus[..., 2]
+    else:
+        square, minus = i * i % q, (i[:, None] - i[None]) % q
+    chi = torch.full((q,), -1.0, dtype=torch.float64)
+    chi[square] = 1.0
+    chi[0] = 0.0
+    P = torch.ones((b, b), dtype=torch.float64)
+    P[1:, 0] = -1.0
+    P[1:, 1:] = chi[minus] + torch.eye(q, dtype=torch.float64)
+    return P.cuda()
+
+
+def _rotate(x, d_e):
+    """Zero padding to d_e and the orthonormal rotation P_b (x) S_n, in 64 bits."""
+    for b in (1, 12, 20, 60, 68, 72, 132, 140, 152, 312, 344):
+        n = d_e // b
+        if n * b == d_e and n & (n - 1) == 0:
+            break
+    T, d = x.shape
+    padded = torch.zeros((T, d_e), dtype=torch.float64, device="cuda")
+    padded[:, :d] = x
+    y = (padded.view(T * b, n) @ _sylvester(n)).view(T, b, n)
+    y = (y.transpose(1, 2).reshape(T * n, b) @ _paley(b)).view(T, n, b).transpose(1, 2)
+    return y.reshape(T, d_e) / d_e ** 0.5
+
+
+def _nibbles(q):
+    """The two codes of each byte, in order."""
+    return torch.stack((q & 15, q >> 4), 2).view(q.shape[0], -1)
+
+
+def _bytes(codes):
+    codes = codes.to(torch.int64) & 15
+    return (codes[:, ::2] | codes[:, 1::2] << 4).to(torch.uint8)
+
+
+def _e2m1(u):
+    table = torch.tensor([0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0], dtype=torch.float64, device="cuda")
+    return torch.where(u < 8, table[(u & 7).long()], -table[(u & 7).long()])
+
+
+def _mxfp4(x):
+    """Codes 0 .. 15 and the exponents of the blocks' scales (OCP microscaling: 2^(floor(log2 max) - 2), round half to
+    even, saturating)."""
+    blocks = x.view(x.shape[0], -1, 32)
+    top = blocks.abs().amax(2)
+    e = torch.frexp(top)[1].to(torch.int64) - 3
+    e = torch.where(top > 0, e, -127).clamp(-127, 127)
+    v = torch.ldexp(blocks, -e[:, :, None])
+    m = v.abs()
+    step = torch.where(m < 2, 0.5, torch.where(m < 4, 1.0, 2.0)).double()
+    m = ((m / step).round() * step).clamp(max=6.0)
+    code = torch.where(m <= 2, m * 2, torch.where(m <= 4, m + 2, m / 2 + 4)).long()
+    return (code + torch.where(v < 0, 8, 0)).view(x.shape), e
+
+
+def exact(case, seed):
+    s = prepare(case, seed)
+    d_e, fmt = case["d_e"], case["format"]
+    x = _rotate(s["wt"] if case["do"] == "weights" else s["x"], d_e)
+    if fmt == "mxfp4":
+        code, e = _mxfp4(x)
+        if case["do"] == "weights":
+            return _bytes(code), (e + 127).to(torch.uint8)
+        scaled = torch.ldexp(_e2m1(code).view(*e.shape, 32), e[:, :, None]).view(x.shape)
+        ew = s["ew"].to(torch.int64) - 127
+        w = torch.ldexp(_e2m1(_nibbles(s["qw"])).view(*ew.shape, 32), ew[:, :, None]).view(s["qw"].shape[0], d_e)
+        return scaled @ w.t()
+    if fmt == "asym":
+        lo, hi = x.amin(1).clamp(max=0.0), x.amax(1).clamp(min=0.0)
+        sx = (hi - lo) / 15
+        z = (-lo / sx).round().clamp(0, 15)
+        code = ((x / sx[:, None]).round() + z[:, None]).clamp(0, 15) - z[:, None]
+    else:
+        sx = x.abs().amax(1) / 7
+        code = (x / sx[:, None]).round().clamp(-8, 7)
+    if case["do"] == "weights":
+        return _bytes(code), sx
+    w = _nibbles(s["qw"]).to(torch.int64)
+    w = torch.where(w < 8, w, w - 16).double()
+    return (code @ w.t()) * sx[:, None] * s["sw"].double()
+
+
 def tolerance(case):
     """Another correct implementation sums the rotation in another order, which moves a code by one where its value lies
     on a rounding boundary; layer outputs are then rounded to bf16.  Four times what the library's two sets of kernels
