@@ -35,6 +35,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr int kMaxWaves = 10;   // waves per workgroup: 10 column tiles of 16 (order 160) at one tile per wave
+constexpr int kRedSlots = 16;   // per-wave maxima (minima) in LDS: one per lane of a row, unused ones neutral
 
 template <int KLOG2> struct Layout {
     static constexpr int NC = 1 << KLOG2;      // FWHT length
@@ -130,14 +131,32 @@ template <int KLOG2> __device__ __forceinline__ int run_start(int l4, int l5) {
     return L::RUN * (l4 + 2 * l5);
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+// Reductions over the 16 lanes of a row and over the wavefront, result in every lane: data-parallel moves within the
+// row (xor 1, xor 2, mirrored halves, mirrored row), then the two row swaps.  A chain of vector instructions; the same
+// steps through ds_bpermute cost an LDS round trip each, twelve in a row for the asymmetric range, which no other work
+// of the wave covers.
+template <class Op> __device__ __forceinline__ float row_reduce(float v, Op op) {
+    auto step = [&](auto ctrl) {
+        const int moved = __builtin_amdgcn_mov_dpp((int)__float_as_uint(v), decltype(ctrl)::value, 0xF, 0xF, true);
+        v = op(v, __uint_as_float((uint32_t)moved));
+    };
+    step(std::integral_constant<int, 0xB1>{});     // quad_perm [1, 0, 3, 2]
+    step(std::integral_constant<int, 0x4E>{});     // quad_perm [2, 3, 0, 1]
+    step(std::integral_constant<int, 0x141>{});    // row_half_mirror
+    step(std::integral_constant<int, 0x140>{});    // row_mirror
     return v;
 }
-__device__ __forceinline__ float wave_min(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off));
-    return v;
+template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op op) {
+    v = row_reduce(v, op);
+    float a = v, b = v;
+    swap16(a, b);
+    a = op(a, b);
+    b = a;
+    swap32(a, b);
+    return op(a, b);
 }
+struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fmaxf(a, b); } };
+struct OpMin { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fminf(a, b); } };
 
 // bf16 bits of the truncation of f, and the exact remainder.
 __device__ __forceinline__ uint32_t split_hi(float f, float& rem) {
@@ -282,7 +301,8 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     const int plane_bytes = ks_count * MT * 1024;     // one bf16 copy of the K-padded token
 
     extern __shared__ __align__(1024) unsigned char smem[];   // NS token planes, then the B fragments
-    __shared__ float red[2 * kMaxWaves];
+    __shared__ float red[2 * kRedSlots];
+    static_assert(kMaxWaves <= kRedSlots, "a row of 16 lanes reduces the waves' ranges");
 
     static_assert(!(MULTI && F32IN), "the multi-token variant takes bf16 input");
     const int lane = threadIdx.x & 63, wave_hw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves_hw = blockDim.x >> 6;
@@ -365,6 +385,10 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
         }
     };
 
+    if constexpr (OUT == OUT_SYM || OUT == OUT_ASYM) {
+        // the slots of waves that do not exist; the first barrier of the token loop separates this from their readers
+        if (threadIdx.x < 2 * kRedSlots && (int)(threadIdx.x % kRedSlots) >= nwaves) red[threadIdx.x] = 0.f;
+    }
     const int64_t t_step = MULTI ? (int64_t)gridDim.x * nwaves_hw : gridDim.x;
     int64_t t = MULTI ? (int64_t)blockIdx.x * nwaves_hw + wave_hw : blockIdx.x;
     if constexpr (!F32IN) {
@@ -565,22 +589,22 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
                     hi = __builtin_fmaxf(__builtin_fmaxf(hi, v[ti][i]), v[ti][i + 1]);
                     lo = __builtin_fminf(__builtin_fminf(lo, v[ti][i]), v[ti][i + 1]);
                 }
-            lo = wave_min(lo);
+            lo = wave_reduce(lo, OpMin{});
         } else {
 #pragma unroll
             for (int ti = 0; ti < TPW; ++ti)
 #pragma unroll
                 for (int i = 0; i < NREG; i += 2) hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(v[ti][i])), __builtin_fabsf(v[ti][i + 1]));
         }
-        hi = wave_max(hi);
+        hi = wave_reduce(hi, OpMax{});
         if (nwaves > 1) {
             // the scratch is reused per token: the barrier of the matrix phase separates the tokens
-            if (lane == 0) { red[wave] = hi; red[kMaxWaves + wave] = lo; }
+            if (lane == 0) { red[wave] = hi; red[kRedSlots + wave] = lo; }
             lds_barrier();
-            for (int w = 0; w < nwaves; ++w) {
-                hi = fmaxf(hi, red[w]);
-                lo = fminf(lo, red[kMaxWaves + w]);
-            }
+            // lane l of a row takes wave l's value (0, which changes neither range, beyond the last wave): one read and
+            // four steps in place of one dependent read per wave
+            hi = row_reduce(red[l15], OpMax{});
+            if constexpr (OUT == OUT_ASYM) lo = row_reduce(red[kRedSlots + l15], OpMin{});
         }
 
         float s = 1.f, rinv = 0.f;
