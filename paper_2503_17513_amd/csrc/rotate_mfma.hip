@@ -158,11 +158,11 @@ template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op op)
 struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fmaxf(a, b); } };
 struct OpMin { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fminf(a, b); } };
 
-// bf16 bits of the truncation of f, and the exact remainder.
-__device__ __forceinline__ uint32_t split_hi(float f, float& rem) {
-    const uint32_t hi = __float_as_uint(f) & 0xFFFF0000u;
-    rem = f - __uint_as_float(hi);
-    return hi >> 16;
+// Exact remainder of f after its truncation to bf16 (the upper half of its bits).
+__device__ __forceinline__ float split_rem(float f) { return f - __uint_as_float(__float_as_uint(f) & 0xFFFF0000u); }
+// The upper halves of two fp32 values in one dword, f0's in the low half.
+__device__ __forceinline__ uint32_t upper_halves(float f0, float f1) {
+    return __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -280,6 +280,12 @@ template <int KLOG2, int TPW> constexpr int max_waves() {
     return ((TPW == 1 && KLOG2 <= 8) || KLOG2 == 6) ? kMaxWaves : kMaxWaves / 2;
 }
 
+// fp32 input: K steps of the base block whose three bf16 term planes are in LDS at a time -- 48 KB of planes at 2^k = 64 ..
+// 256, so that three workgroups share a compute unit -- and the 4-column x 8-row units of the following ones that each
+// thread fetches ahead into registers (one unit a thread covers them with 4 waves; 32 registers a unit).
+template <int KLOG2> constexpr int f32_ksteps() { return KLOG2 == 6 ? 4 : KLOG2 <= 7 ? 2 : 1; }
+template <int KLOG2> constexpr int f32_ahead() { return KLOG2 == 9 ? 2 : 1; }
+
 enum { OUT_SYM = 0, OUT_ASYM = 1, OUT_XHAT = 2, OUT_MXFP4 = 3 };   // int4 symmetric / asymmetric codes, fp32 values, MXFP4
 
 // MULTI: a token fits one wave (all its tiles are this wave's TPW tiles), and every wave of the workgroup
@@ -298,7 +304,8 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     using L = Layout<KLOG2>;
     constexpr int NC = L::NC, MT = L::MT, NREG = L::NREG;
     constexpr int NS = F32IN ? 3 : 1;
-    const int plane_bytes = ks_count * MT * 1024;     // one bf16 copy of the K-padded token
+    constexpr int KG = f32_ksteps<KLOG2>();
+    const int plane_bytes = (F32IN ? KG : ks_count) * MT * 1024;     // one bf16 copy of the K-padded token (fp32: of KG K steps)
 
     extern __shared__ __align__(1024) unsigned char smem[];   // NS token planes, then the B fragments
     __shared__ float red[2 * kRedSlots];
@@ -351,38 +358,49 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
             if (off < 2u * (uint32_t)d) dma16(xr, off, __builtin_amdgcn_readfirstlane(lds0 + base * 16));
         }
     };
-    // fp32 token: split every input into three bf16 terms (exact sum) and store each term plane in
-    // A-fragment order: fragment (ks, mt), slot (c % 16) + 16 g holds the 8 values a = 32 ks + 8 g + e of
-    // column c = 16 mt + c % 16.
-    auto load_token_f32 = [&](int64_t t) {
+    // fp32 token, KG K steps at a time: every input is split once into three bf16 terms (exact sum), and each term plane
+    // is stored in A-fragment order: fragment (ks, mt), slot (c % 16) + 16 g holds the 8 values a = 32 ks + 8 g + e of
+    // column c = 16 mt + c % 16.  What bounds this path is the chain load -> split -> LDS -> matrix cores, so the loads
+    // of the next K steps (or token) are issued as soon as the registers of the current ones are split, and fly under
+    // the matrix, FWHT and quantize phases; with only KG K steps of planes, several workgroups share a compute unit.
+    // (4096 rows of 14336 -> 15360, 266 MB: 178 us with the whole token's planes, 96 KB, filled without prefetch and one
+    // workgroup per compute unit, 70 us so.)
+    // A unit is 4 columns x 8 rows: 16-byte loads, and the four 16-byte stores of a lane go to slots whose low bits are
+    // XORed with mt so that the 16 slots of a bank round are all different.
+    constexpr int AHEAD = f32_ahead<KLOG2>(), UNITS = KG * NC, UPR = NC / 4;      // units of a phase; units per 8-row group
+    f32x4 ahead[F32IN ? AHEAD : 1][8];
+    const bool vec4 = F32IN && (reinterpret_cast<uintptr_t>(xv) & 15) == 0 && (ldx & 3) == 0 && (d & 3) == 0;
+    // Only rows that 16-byte loads can take are fetched ahead; everything else goes column by column in the phase itself.
+    auto load_ahead = [&](int64_t t, int phase) {
         const float* xr = static_cast<const float*>(xv) + t * ldx;
-        const int units = ks_count * 4 * NC;
-        for (int u = tid; u < units; u += nthreads) {
-            const int c = u % NC, ag = u / NC;
-            const int a0 = 8 * ag;
-            uint32_t h0[8], h1[8], h2[8];
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            const int u = tid + s * nthreads;
+            if (!vec4 || u >= UNITS) continue;
+            const int i0 = (32 * KG * phase + 8 * (u / UPR)) * NC + 4 * (u % UPR);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int i = (a0 + e) * NC + c;
-                const float f = (i < d) ? xr[i] : 0.f;
-                float r1, r2, r3;
-                h0[e] = split_hi(f, r1);
-                h1[e] = split_hi(r1, r2);
-                h2[e] = split_hi(r2, r3);
+                ahead[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (i0 + e * NC < d) ahead[s][e] = *reinterpret_cast<const f32x4*>(xr + (uint32_t)(i0 + e * NC));
             }
-            const int ks = ag >> 2, gg = ag & 3, mt = c >> 4;
-            unsigned char* dst = tsm + ((size_t)((ks * MT + mt) * 64 + (c & 15) + 16 * gg)) * 16;
-            u32x4 p0, p1, p2;
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                p0[p] = h0[2 * p] | (h0[2 * p + 1] << 16);
-                p1[p] = h1[2 * p] | (h1[2 * p + 1] << 16);
-                p2[p] = h2[2 * p] | (h2[2 * p + 1] << 16);
-            }
-            *reinterpret_cast<u32x4*>(dst) = p0;
-            *reinterpret_cast<u32x4*>(dst + plane_bytes) = p1;
-            *reinterpret_cast<u32x4*>(dst + 2 * plane_bytes) = p2;
         }
+    };
+    // the 8 rows of column j of unit u: three 16-byte slots
+    auto split_column = [&](int u, int j, auto row) {
+        const int ag = u / UPR, c4 = u % UPR, mt = c4 >> 2;
+        unsigned char* dst = tsm + (size_t)((ag >> 2) * MT + mt) * 1024 + 16 * ((4 * (c4 & 3) + 16 * (ag & 3) + j) ^ (mt & 3));
+        u32x4 p0, p1, p2;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float f0 = row(2 * p), f1 = row(2 * p + 1);
+            const float r0 = split_rem(f0), r1 = split_rem(f1);
+            p0[p] = upper_halves(f0, f1);
+            p1[p] = upper_halves(r0, r1);
+            p2[p] = upper_halves(split_rem(r0), split_rem(r1));
+        }
+        *reinterpret_cast<u32x4*>(dst) = p0;
+        *reinterpret_cast<u32x4*>(dst + plane_bytes) = p1;
+        *reinterpret_cast<u32x4*>(dst + 2 * plane_bytes) = p2;
     };
 
     if constexpr (OUT == OUT_SYM || OUT == OUT_ASYM) {
@@ -393,6 +411,8 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     int64_t t = MULTI ? (int64_t)blockIdx.x * nwaves_hw + wave_hw : blockIdx.x;
     if constexpr (!F32IN) {
         if (t < T) load_token_dma(t);       // in flight while the B fragments are fetched
+    } else {
+        if (t < T) load_ahead(t, 0);
     }
     // ---- once per workgroup: B fragments of P into LDS
     static_assert(KSREG == 0 || BGLOBAL, "register-resident fragments come from the table in device memory");
@@ -431,13 +451,34 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     const float g7 = (float)(gamma / 7.0), g15 = (float)(gamma / 15.0);
 
     for (; t < T; t += t_step) {
-        if constexpr (F32IN) {
-            lds_barrier();                  // every wave has finished reading the previous token
-            load_token_f32(t);
-        } else {
+        if constexpr (!F32IN) {
             wait_all_vm();                  // this wave's part of the token (and its earlier stores) has landed
+            token_sync();
         }
-        token_sync();
+        // fp32: the planes of K steps KG phase .. KG phase + KG - 1 of this token; then the next loads
+        auto f32_phase = [&](int phase) {
+            lds_barrier();                  // every wave has finished reading the previous planes
+            if (vec4) {
+#pragma unroll
+                for (int s = 0; s < AHEAD; ++s)
+                    if (tid + s * nthreads < UNITS) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) split_column(tid + s * nthreads, j, [&](int e) { return ahead[s][e][j]; });
+                    }
+            }
+            // workgroups of few waves have more units than they fetched ahead; unaligned rows fetch nothing ahead
+            const float* xr = static_cast<const float*>(xv) + t * ldx;
+#pragma unroll 1
+            for (int uj = tid + (vec4 ? AHEAD * nthreads : 0); uj < UNITS; uj += nthreads)
+#pragma unroll 1
+                for (int j = 0; j < 4; ++j) {
+                    const int i0 = (32 * KG * phase + 8 * (uj / UPR)) * NC + 4 * (uj % UPR) + j;
+                    split_column(uj, j, [&](int e) { return i0 + e * NC < d ? xr[(uint32_t)(i0 + e * NC)] : 0.f; });
+                }
+            if (KG * (phase + 1) < ks_count) load_ahead(t, phase + 1);
+            else if (t + t_step < T) load_ahead(t + t_step, 0);
+            lds_barrier();
+        };
 
         // ---- base block on the matrix cores: Z^T[c][a'] = sum_a X~[a][c] P[a][a']
         f32x4 acc[TPW][MT];
@@ -466,7 +507,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
 #pragma unroll
                     for (int sp = 0; sp < NS; ++sp) {
                         const u32x4 raw = *reinterpret_cast<const u32x4*>(
-                            tsm + (size_t)sp * plane_bytes + ((size_t)((ks * MT + mt) * 64 + lane)) * 16);
+                            tsm + (size_t)sp * plane_bytes + ((size_t)(((ks & (KG - 1)) * MT + mt) * 64 + (lane ^ (mt & 3)))) * 16);
                         const bf16x8 af = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
                         for (int ti = 0; ti < TPW; ++ti)
@@ -479,6 +520,9 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
         if constexpr (KSREG > 0) {
             static_for<KSREG>([&](auto kc) {
                 constexpr int KS = decltype(kc)::value;
+                if constexpr (F32IN && KS % KG == 0) {
+                    if (KS < ks_count) f32_phase(KS / KG);
+                }
                 auto from_regs = [&](int ti) { return __builtin_bit_cast(bf16x8, breg[ti][KS]); };
                 if constexpr (KS == 0) base_block(0, std::true_type{}, from_regs);
                 else if (KS < ks_count) base_block(KS, std::false_type{}, from_regs);       // wave-uniform
@@ -492,8 +536,14 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
                         return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(bsm + ((size_t)(ti * ks_count + ks) * 64 + lane) * 16));
                 };
             };
+            if constexpr (F32IN) f32_phase(0);
             base_block(0, std::true_type{}, from_memory(0));
-            for (int ks = 1; ks < ks_count; ++ks) base_block(ks, std::false_type{}, from_memory(ks));
+            for (int ks = 1; ks < ks_count; ++ks) {
+                if constexpr (F32IN) {
+                    if (ks % KG == 0) f32_phase(ks / KG);
+                }
+                base_block(ks, std::false_type{}, from_memory(ks));
+            }
         }
 
         if constexpr (!F32IN) {
@@ -701,7 +751,7 @@ template <int KLOG2, int TPW, bool F32IN, int OUT, bool BGLOBAL = false, int KSR
 pme_status launch_out(const RotateArgs& a, int ks, int nwaves) {
     using L = Layout<KLOG2>;
     constexpr int NS = F32IN ? 3 : 1;
-    const size_t lds = (size_t)NS * ks * L::MT * 1024 + (BGLOBAL ? 0 : (size_t)nwaves * TPW * ks * 1024);
+    const size_t lds = (size_t)NS * (F32IN ? f32_ksteps<KLOG2>() : ks) * L::MT * 1024 + (BGLOBAL ? 0 : (size_t)nwaves * TPW * ks * 1024);
     // 160 KB per workgroup, less the kernel's static LDS rounded up to the dynamic part's 1 KB alignment
     constexpr size_t kMaxDynLds = 160 * 1024 - 1024;
     if (lds > kMaxDynLds || nwaves > max_waves<KLOG2, TPW>()) return PME_ERR_UNSUPPORTED_PATH;
@@ -836,24 +886,26 @@ pme_status launch_rotate_mfma(const RotateArgs& in) {
     //  * 2^k = 128 (8704): 4 % faster.
     // Where a wave's fragments are few (TPW x K steps <= 8 registers of 16 bytes), it reads them once and keeps
     // them in registers for all its tokens: another 3-6 % (8448 .. 9728, 8704, 15360).
-    if (!f32 && g_tpw_override == 0) {
+#define PME_ROTG(K, TP, KS, NWAVES) (f32 ? launch_one<K, TP, true, true, KS>(a, ks, NWAVES) : launch_one<K, TP, false, true, KS>(a, ks, NWAVES))
+    if (g_tpw_override == 0) {
         if (a.k == 6 && nt >= 8) {
             // from about 3000 tokens three tiles per wave (three waves per token, five tokens in flight per compute
             // unit) beat two (8448 .. 9728: 5-11 % at 4096 and 8192 tokens; 1-4 % slower at 2048)
-            if (nt <= 16 && ks <= 4 && a.T >= 3072) return launch_one<6, 3, false, true, 4>(a, ks, (nt + 2) / 3);
+            if (!f32 && nt <= 16 && ks <= 4 && a.T >= 3072) return launch_one<6, 3, false, true, 4>(a, ks, (nt + 2) / 3);
             // a handful of tokens (decode): one tile per wave, nine or ten waves per token; the kernel is a chain of
             // latencies there and the lighter waves shorten it (8448, 8 tokens: 4.1 -> 3.8 us)
-            if (nt <= kMaxWaves && ks <= 4 && a.T <= 64) return launch_one<6, 1, false, true, 4>(a, ks, nt);
-            if (nt <= 2 * kMaxWaves && ks <= 4) return launch_one<6, 2, false, true, 4>(a, ks, (nt + 1) / 2);
+            if (nt <= kMaxWaves && ks <= 4 && a.T <= 64) return PME_ROTG(6, 1, 4, nt);
+            if (nt <= 2 * kMaxWaves && ks <= 4) return PME_ROTG(6, 2, 4, (nt + 1) / 2);
             // beyond 16 tiles three per wave: 7 waves for the order-312 block, so that two workgroups share a compute
             // unit (19968: 42 -> 36 us for 2048 tokens against 10 waves of two tiles)
-            if (nt <= 16) return launch_one<6, 2, false, true>(a, ks, (nt + 1) / 2);
-            return launch_one<6, 3, false, true>(a, ks, (nt + 2) / 3);
+            if (nt <= 16) return PME_ROTG(6, 2, 0, (nt + 1) / 2);
+            return PME_ROTG(6, 3, 0, (nt + 2) / 3);
         }
-        if (a.k == 7 && tpw == 2 && ks <= 2) return launch_one<7, 2, false, true, 2>(a, ks, (nt + 1) / 2);
-        if (a.k == 7 && tpw == 2) return launch_one<7, 2, false, true>(a, ks, (nt + 1) / 2);
-        if (a.k == 8 && tpw == 1 && ks <= 2) return launch_one<8, 1, false, true, 2>(a, ks, nt);
+        if (a.k == 7 && tpw == 2 && ks <= 2) return PME_ROTG(7, 2, 2, (nt + 1) / 2);
+        if (a.k == 7 && tpw == 2) return PME_ROTG(7, 2, 0, (nt + 1) / 2);
+        if (a.k == 8 && tpw == 1 && ks <= 2) return PME_ROTG(8, 1, 2, nt);
     }
+#undef PME_ROTG
     const int nwaves = (nt + tpw - 1) / tpw;
     if (nwaves > kMaxWaves) return PME_ERR_UNSUPPORTED_PATH;
     // 2^k = 32 with a block of at most 80: the token is one wave's work and only a few KB

@@ -100,6 +100,32 @@ def test_rotate_and_quantize(name, T, d, d_e, in_dtype, paths):
             assert np.all(np.abs(unpack_gpu(qx)[2]) == 7)
 
 
+# fp32 input on the matrix cores: tokens are split into term planes a few K steps at a time, the next ones fetched ahead.
+# One and several phases per token (2^k = 32 .. 512), workgroups with more and with fewer threads than a phase has units,
+# more tokens than the persistent grid, d that ends inside a base row, and rows that 16-byte loads cannot take.
+F32_CASES = [("k5_two_ks", 5, 2048, 2176, 0), ("k5_one_ks", 5, 500, 640, 0), ("k6_one_wave", 4, 696, 768, 0),
+             ("k6_grid_wraps", 1700, 696, 768, 0), ("k6_four_ks", 70, 8192, 9728, 0), ("k6_five_ks", 3, 14336, 19968, 0),
+             ("k6_b344", 3, 14000, 22016, 0), ("k7_one_phase", 520, 8192, 8704, 0), ("k7_few_tokens", 9, 8192, 8704, 0),
+             ("k8_two_phases", 6, 14336, 15360, 0), ("k8_five_waves", 4, 14336, 18432, 0), ("k8_one_wave", 4, 2500, 3072, 0),
+             ("k9_two_phases", 2, 30000, 32768, 0),
+             ("k6_base_off_by_4_bytes", 5, 8192, 8448, 1), ("k8_ragged_odd_d", 4, 14001, 15360, 1), ("k7_odd_d", 4, 8191, 8704, 0)]
+
+
+@pytest.mark.parametrize("name,T,d,d_e,shift", F32_CASES, ids=[c[0] for c in F32_CASES])
+def test_rotate_fp32_on_the_matrix_cores(name, T, d, d_e, shift):
+    x = _acts(T, d, d_e, "f32", seed=len(name))
+    wide = torch.full((T, d + 3 * shift), 7.0, device="cuda")
+    xd = wide[:, shift:shift + d]                   # shift: an odd pitch and a base that is 4-byte aligned only
+    xd.copy_(torch.from_numpy(x))
+    ref = oracle.rotate_structured(x, d_e)
+    q_ref, s_ref = oracle.quantize_sym_int4(ref)
+    pme.set_path(MFMA)
+    check_xhat(pme.hadamard_expand_f32(xd, d_e).cpu().numpy(), ref)
+    qx, sx = pme.hadamard_expand_quant(xd, d_e)
+    check_scales(sx.cpu().numpy(), s_ref)
+    check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
+
+
 @pytest.mark.parametrize("path", (GENERIC, MFMA))
 def test_rotate_strided_rows(path):
     # ldx > d: rows of a wider buffer
