@@ -1,0 +1,373 @@
+// W4A4 GEMM for outputs that give a compute unit one small tile: the four waves of a workgroup split K.
+//
+//   acc[t][n] = sum_j qx[t][j] qw[n][j],  y[t][n] = bf16(acc * sx[t] * sw[n])   (paper Sections 3 and 4).
+//
+// A workgroup owns a 32 FM x 32 FN output tile.  Wave w takes the K steps w, w + 4, w + 8, ... (128 codes each) and
+// computes the whole tile over them, from an LDS ring of its own that it fills by DMA itself: there is no barrier in
+// the K loop, and against waves that share the tile's quarters each fragment read and unpacked feeds twice the matrix
+// instructions.  What bounds the tiled kernel at these sizes is that one wave per SIMD meets a workgroup barrier every
+// 256 codes with little matrix work in between; here a wave only ever waits for its own DMA.  The partial tiles
+// (exact integers) are added through LDS at the end, four 32 x 32 blocks at a time, one per wave, and each wave
+// finishes the block that it added.
+// Operands, unpacking (a nibble in the top of a byte is 16 x its value), fragment layout and epilogue as in gemm_mfma.hip.
+#include "gemm_tile.h"
+
+#include <algorithm>
+#include <cstdio>
+#include <string>
+
+namespace pme {
+namespace {
+
+// LDS of the rings (NSTAGE stages of 64 bytes a row for every wave), which also hold a round of partial blocks (four
+// blocks of 4 KB of every wave) and the finished parts (8 KB in all).
+constexpr int kslice_lds_rings(int bm, int bn, int nw, int nstage) {
+    const int blocks = (bm / 32) * (bn / 32);
+    const int rings = nw * nstage * (bm + bn) * 64, parts = (blocks < 4 ? blocks : 4) * nw * 4096 + 8192;
+    return rings > parts ? rings : parts;
+}
+
+// NW: waves (slices of K), 4 or 8: one or two per SIMD.
+template <int BM, int BN, int NW, int NSTAGE, int MODE>
+__global__ void __launch_bounds__(64 * NW)
+k_gemm_kslice(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ qw,
+              const float* __restrict__ sx, const float* __restrict__ sw,
+              const int32_t* __restrict__ zx, const int32_t* __restrict__ wsum,
+              int T, int N, int kb, void* __restrict__ out, int64_t ldo, int tiles_m, int tiles_n, int xcd_gm, int vec_store) {
+    constexpr int FM = BM / 32, FN = BN / 32, ROWS = BM + BN;
+    static_assert(BM % 32 == 0 && BN % 32 == 0, "whole 32-row fragments");
+    constexpr int RB = 64;                        // bytes per row and K step
+    constexpr int CH = ROWS / 16;                 // DMA instructions per stage (16 rows each)
+    constexpr int STAGE = ROWS * RB, RING = NSTAGE * STAGE;
+    constexpr int NBLK = FM * FN;                 // 32 x 32 blocks of the tile
+    constexpr int ROUNDS = (NBLK + 3) / 4;
+    constexpr int BLOCK = 32 * 32 * 4;            // bytes of a partial block
+    constexpr int SHARE = NW / 4, QN = 4 / SHARE; // waves that finish a block together; groups of 8 channels each takes
+    constexpr int SLAB = 32 * 16 * QN;            // bytes of a wave's finished bf16 part
+    static_assert(NW == 4 || NW == 8, "one or two waves per SIMD");
+    constexpr int PART = (NBLK < 4 ? NBLK : 4) * NW * BLOCK;      // a round's four blocks of every wave
+    constexpr int RINGS = kslice_lds_rings(BM, BN, NW, NSTAGE);
+    static_assert(NW * RING <= RINGS && PART + NW * SLAB <= RINGS, "the partial blocks go through the rings");
+
+    extern __shared__ __align__(1024) unsigned char smem[];      // a ring per wave, then the tile's scales
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tm, tn;
+    xcd_tile((int)blockIdx.x, tiles_m, tiles_n, xcd_gm, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    unsigned char* ring = smem + wave * RING;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(PME_AS3 unsigned char*)ring;
+    const int KT = kb / RB;                                      // K steps in all
+    const int steps = __builtin_amdgcn_readfirstlane((KT - wave + NW - 1) / NW);       // this wave's, at least one
+
+    // DMA: block blk covers tile rows 16 blk .. 16 blk + 15; lane L fills chunk position L % 4 of row L / 4, which holds
+    // chunk (L % 4) ^ swz(row) (the swizzle looks at the row's low four bits only)
+    uint32_t voff[CH];
+    {
+        const int lr = lane >> 2, kc = (lane & 3) ^ swz<RB>(lr);
+#pragma unroll
+        for (int blk = 0; blk < CH; ++blk) {
+            const int r = 16 * blk + lr;
+            const int row = (r < BM) ? min(m0 + r, T - 1) : min(n0 + r - BM, N - 1);
+            voff[blk] = (uint32_t)row * (uint32_t)kb + (uint32_t)(kc * 16);
+        }
+    }
+    // the i-th of this wave's steps (beyond the last one: the last K step again, into a stage that nobody reads, so that
+    // every step issues the same number of DMA instructions and the wait counts are constants)
+    auto step_offset = [&](int i) { return __builtin_amdgcn_readfirstlane(min(wave + NW * i, KT - 1) * RB); };
+    auto issue_slot = [&](int stage, int koff, int blk) {
+        dma16((blk < BM / 16 ? qx : qw) + koff, voff[blk], __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE + blk * 1024));
+    };
+    // scales (with 1/256, which removes the 16 x 16 of the nibble trick) and the asymmetric terms: fetched now, parked in
+    // LDS for the epilogue
+    constexpr int NT = 64 * NW, PRE = (ROWS + NT - 1) / NT;
+    float pre[PRE];
+    int prez[PRE];
+#pragma unroll
+    for (int q = 0; q < PRE; ++q) {
+        const int idx = tid + NT * q;
+        pre[q] = 0.f;
+        prez[q] = 0;
+        if constexpr (MODE != MODE_I32) {
+            if (idx < BM) pre[q] = sx[min(m0 + idx, T - 1)] * (MODE == MODE_ASYM ? 1.f : 1.f / 256.f);
+            else if (idx < ROWS) pre[q] = sw[min(n0 + idx - BM, N - 1)];
+        }
+        if constexpr (MODE == MODE_ASYM) {
+            if (idx < BM) prez[q] = zx[min(m0 + idx, T - 1)];
+            else if (idx < ROWS) prez[q] = wsum[min(n0 + idx - BM, N - 1)];
+        }
+    }
+    float* sc = reinterpret_cast<float*>(smem + RINGS);
+    int* zc = reinterpret_cast<int*>(sc + ROWS);
+    if constexpr (MODE != MODE_I32) {
+#pragma unroll
+        for (int q = 0; q < PRE; ++q) {
+            const int idx = tid + NT * q;
+            if (idx < ROWS) {
+                sc[idx] = pre[q];
+                if constexpr (MODE == MODE_ASYM) zc[idx] = prez[q];
+            }
+        }
+    }
+
+    i32x16 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0;
+
+    const int frow = lane & 31, fk = lane >> 5;
+    // sub-step s of a step reads chunk 2 s + fk, at position (fk ^ swz(r)) ^ 2 s; rows 32 i + frow share frow's swizzle
+    const int off0 = frow * RB + ((fk ^ swz<RB>(frow)) << 4);
+    struct Frags { u32x4 a[FM], b[FN]; };
+    struct Unpacked { i32x4 alo[FM], ahi[FM], blo[FN], bhi[FN]; };
+    auto load_frags = [&](Frags& f, const unsigned char* stage, int s) {
+        const unsigned char *pa = stage + (off0 ^ (s << 5)), *pb = pa + BM * RB;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) f.a[i] = *reinterpret_cast<const u32x4*>(pa + 32 * i * RB);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) f.b[j] = *reinterpret_cast<const u32x4*>(pb + 32 * j * RB);
+    };
+    // part c of NPART of the fragments' dwords / of the matrix instructions
+    constexpr int NITEM = 4 * (FM + FN), NMFMA = 2 * FM * FN;
+    auto unpack_part = [&](const Frags& f, Unpacked& u, int c, int nparts) {
+#pragma unroll
+        for (int q = 0; q < NITEM; ++q) {
+            if (q * nparts / NITEM != c) continue;
+            const int fr = q >> 2, e = q & 3;
+            if (fr < FM) {
+                uint32_t w = f.a[fr][e];
+                if (MODE == MODE_ASYM) w ^= 0x88888888u;
+                u.alo[fr][e] = (int)((w & 0x0F0F0F0Fu) << 4);
+                u.ahi[fr][e] = (int)(w & 0xF0F0F0F0u);
+            } else {
+                const uint32_t w = f.b[fr - FM][e];
+                u.blo[fr - FM][e] = (int)((w & 0x0F0F0F0Fu) << 4);
+                u.bhi[fr - FM][e] = (int)(w & 0xF0F0F0F0u);
+            }
+        }
+    };
+    auto mfma_part = [&](const Unpacked& u, int c, int nparts) {
+#pragma unroll
+        for (int m = 0; m < NMFMA; ++m) {
+            if (m * nparts / NMFMA != c) continue;
+            const int i = m / (2 * FN), j = (m >> 1) % FN;
+            if ((m & 1) == 0) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(u.blo[j], u.alo[i], acc[i][j], 0, 0, 0);
+            else acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(u.bhi[j], u.ahi[i], acc[i][j], 0, 0, 0);
+        }
+    };
+    constexpr int NVALU = (FM + FN) * 12 + (MODE == MODE_ASYM ? FM * 4 : 0);
+    constexpr int VPM = (NVALU + NMFMA - 1) / NMFMA;
+    // A region: fragments of sub-step g + 2 are read, those of g + 1 unpacked, the matrix cores work on g; ND DMA
+    // instructions (slots D0 ..) go between the matrix instructions, which keep the pipe busy meanwhile.
+    auto region = [&](Frags& fill, const unsigned char* stage, int s, const Frags& next, Unpacked& unext, const Unpacked& now,
+                      int dst, int koff, auto d0, auto nd) {
+        constexpr int D0 = decltype(d0)::value, ND = decltype(nd)::value, NP = ND > 0 ? ND : 1;
+        load_frags(fill, stage, s);
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+            unpack_part(next, unext, c, NP);
+            mfma_part(now, c, NP);
+            if (c == 0) __builtin_amdgcn_sched_group_barrier(0x100, FM + FN, 0);
+            constexpr int MPP = (NMFMA + NP - 1) / NP;
+#pragma unroll
+            for (int m = 0; m < MPP; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
+            }
+            if constexpr (ND > 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                issue_slot(dst, koff, D0 + c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+
+#pragma unroll
+    for (int st = 0; st < NSTAGE; ++st) {
+        const int koff = step_offset(st);
+#pragma unroll
+        for (int blk = 0; blk < CH; ++blk) issue_slot(st, koff, blk);
+    }
+    wait_vm<(NSTAGE - 1) * CH>();
+    Frags raw[2];
+    Unpacked unp[2];
+    load_frags(raw[0], ring, 0);
+    load_frags(raw[1], ring, 1);
+    unpack_part(raw[0], unp[0], 0, 1);
+    // With two stages the refill must be under way early in the step; with more it is spread over the whole step.
+    constexpr int DMA0 = NSTAGE == 2 ? CH : CH / 2;
+    auto k_step = [&](int i, int cs) {
+        const int nxt = (cs == NSTAGE - 1) ? 0 : cs + 1;
+        const unsigned char* snxt = ring + nxt * STAGE;
+        const int koff = step_offset(i + NSTAGE);
+        // the next step has landed, and every read of this one has left the stage that is refilled now
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NSTAGE - 2) * CH) : "memory");
+        region(raw[0], snxt, 0, raw[1], unp[1], unp[0], cs, koff, std::integral_constant<int, 0>{}, std::integral_constant<int, DMA0>{});
+        region(raw[1], snxt, 1, raw[0], unp[0], unp[1], cs, koff, std::integral_constant<int, DMA0>{}, std::integral_constant<int, CH - DMA0>{});
+    };
+    int cur = 0;
+    for (int i = 0; i + 1 < steps; ++i) {
+        k_step(i, cur);
+        cur = (cur == NSTAGE - 1) ? 0 : cur + 1;
+    }
+    // the last step: its first sub-step is unpacked, its second read
+    unpack_part(raw[1], unp[1], 0, 1);
+    mfma_part(unp[0], 0, 1);
+    mfma_part(unp[1], 0, 1);
+    wait_vm<0>();
+
+    // ---- partial tiles: in rounds of four blocks every wave writes its partial blocks to LDS, then adds and finishes
+    // block 4 round + wave / SHARE (with two waves per block, half of its channels each)
+    unsigned char* slab = smem + PART + wave * SLAB;
+    static_for<ROUNDS>([&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        lds_barrier();                  // the rings, or the previous round's blocks, have been read
+        static_for<4>([&](auto bc) {
+            constexpr int B = 4 * R + decltype(bc)::value;
+            if constexpr (B < NBLK) {
+                unsigned char* p = smem + (decltype(bc)::value * NW + wave) * BLOCK + lane * 16;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<i32x4*>(p + q * 1024) = i32x4{acc[B / FN][B % FN][4 * q], acc[B / FN][B % FN][4 * q + 1],
+                                                                    acc[B / FN][B % FN][4 * q + 2], acc[B / FN][B % FN][4 * q + 3]};
+            }
+        });
+        lds_barrier();
+        const int blk = 4 * R + wave / SHARE, q0 = (wave % SHARE) * QN;
+        if (blk < NBLK) {               // wave-uniform
+            i32x4 sum[QN];
+#pragma unroll
+            for (int q = 0; q < QN; ++q) {
+                sum[q] = i32x4{0, 0, 0, 0};
+#pragma unroll
+                for (int w = 0; w < NW; ++w)
+                    sum[q] += *reinterpret_cast<const i32x4*>(smem + ((wave / SHARE) * NW + w) * BLOCK + (q0 + q) * 1024 + lane * 16);
+            }
+            const int bi = blk / FN, bj = blk % FN;
+            const int tbase = m0 + 32 * bi, cbase = 32 * bj + 8 * q0, nbase = n0 + cbase;
+            // element 4 q + e of the part: channel 8 q + 4 fk + e, token frow
+            if constexpr (MODE == MODE_I32) {
+#pragma unroll
+                for (int q = 0; q < QN; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int n = nbase + 8 * q + 4 * fk + e;
+                        if (tbase + frow < T && n < N) static_cast<int32_t*>(out)[(int64_t)(tbase + frow) * ldo + n] = sum[q][e] >> 8;
+                    }
+            } else {
+                constexpr int PITCH = 16 * QN;        // bytes of a slab row: 8 QN channels
+                const float sxs = sc[32 * bi + frow];
+                const int zoff = MODE == MODE_ASYM ? zc[32 * bi + frow] - 8 : 0;
+#pragma unroll
+                for (int q = 0; q < QN; ++q) {
+                    const int cn = BM + cbase + 8 * q + 4 * fk;
+                    float f[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        int a = sum[q][e];
+                        if (MODE == MODE_ASYM) a = (a >> 8) - zoff * zc[cn + e];
+                        f[e] = (float)a * sxs * sc[cn + e];
+                    }
+                    *reinterpret_cast<u32x2*>(slab + frow * PITCH + (8 * q + 4 * fk) * 2) = u32x2{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3])};
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the slab is this wave's own
+                uint16_t* y = static_cast<uint16_t*>(out);
+                if (vec_store) {
+#pragma unroll
+                    for (int c = lane; c < 32 * QN; c += 64) {
+                        const int row = c / QN, col = (c % QN) * 8;
+                        if (tbase + row < T && nbase + col < N)
+                            *reinterpret_cast<u32x4*>(y + (int64_t)(tbase + row) * ldo + nbase + col) =
+                                *reinterpret_cast<const u32x4*>(slab + row * PITCH + col * 2);
+                    }
+                } else {
+                    for (int c = lane; c < 32 * 8 * QN; c += 64) {
+                        const int row = c / (8 * QN), col = c % (8 * QN);
+                        if (tbase + row < T && nbase + col < N)
+                            y[(int64_t)(tbase + row) * ldo + nbase + col] = *reinterpret_cast<const uint16_t*>(slab + row * PITCH + col * 2);
+                    }
+                }
+            }
+        }
+    });
+}
+
+template <int BM, int BN, int NW, int NSTAGE> const char* kslice_name(int mode) {
+    auto make = [](int m) {
+        char buf[64];
+        snprintf(buf, sizeof buf, "k_gemm_kslice<%d, %d, %d, %d, %d>", BM, BN, NW, NSTAGE, m);
+        return std::string(buf);
+    };
+    static const std::string names[3] = {make(MODE_BF16), make(MODE_ASYM), make(MODE_I32)};
+    return names[mode].c_str();
+}
+
+}  // namespace
+
+template <int BM, int BN, int NW, int NSTAGE> pme_status launch_kslice(const GemmArgs& a) {
+    const int kb = (int)(a.d_e / 2);
+    if (kb % 64 || kb < 64 * NW) return PME_ERR_UNSUPPORTED_PATH;      // whole K steps, at least one for each wave
+    if ((int64_t)std::max(a.T, a.N) * kb >= (int64_t(1) << 32)) return PME_ERR_UNSUPPORTED_PATH;   // 32-bit DMA offsets
+    if (a.dry) {
+        if (a.plan) *a.plan = kslice_name<BM, BN, NW, NSTAGE>(a.out_i32 ? MODE_I32 : a.zx ? MODE_ASYM : MODE_BF16);
+        return PME_OK;
+    }
+    const int tiles_m = (int)((a.T + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
+    constexpr int lds = kslice_lds_rings(BM, BN, NW, NSTAGE) + (BM + BN) * 8;
+    static_assert(lds <= 160 * 1024, "the rings fit in LDS");
+    static std::atomic<uint32_t> done[3];
+    if (allow_dynamic_lds(k_gemm_kslice<BM, BN, NW, NSTAGE, MODE_BF16>, lds, done[0]) != PME_OK ||
+        allow_dynamic_lds(k_gemm_kslice<BM, BN, NW, NSTAGE, MODE_ASYM>, lds, done[1]) != PME_OK ||
+        allow_dynamic_lds(k_gemm_kslice<BM, BN, NW, NSTAGE, MODE_I32>, lds, done[2]) != PME_OK)
+        return PME_ERR_HIP;
+    const int vec = (a.N % 8 == 0 && a.ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0) ? 1 : 0;
+    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * NW);
+#define PME_LAUNCH(MODE)                                                                                                \
+    hipLaunchKernelGGL((k_gemm_kslice<BM, BN, NW, NSTAGE, MODE>), grid, block, lds, a.stream, a.qx, a.qw, a.sx, a.sw, a.zx, \
+                       a.wsum, (int)a.T, (int)a.N, kb, a.y, a.ldy, tiles_m, tiles_n, xcd_grid_m(tiles_m, tiles_n, BM, BN), vec)
+    if (a.out_i32) PME_LAUNCH(MODE_I32);
+    else if (a.zx) PME_LAUNCH(MODE_ASYM);
+    else PME_LAUNCH(MODE_BF16);
+#undef PME_LAUNCH
+    return hip_status(hipGetLastError());
+}
+
+// The caller has checked that d_e % 128 == 0, that d_e is in the accumulator's range and that code rows are 16-byte aligned.
+// Two waves per SIMD where their registers and rings allow (up to 64 x 64): one alone issues a vector instruction only
+// every five cycles and could not unpack as fast as the matrix cores consume (64 x 64, 333 x 2048 x 9728: 11.5 us with
+// four waves, 10.1 with eight).  32 x 32 with two stages leaves room for two workgroups per compute unit (128 x 4096 x
+// 8704: 13.1 us with four stages, 11.5 with two).
+pme_status launch_gemm_kslice(const GemmArgs& a, int tile) {
+    switch (tile) {
+        case 0: return launch_kslice<32, 32, 8, 2>(a);
+        case 1: return launch_kslice<64, 32, 8, 3>(a);
+        case 2: return launch_kslice<64, 64, 8, 2>(a);
+        case 3: return launch_kslice<96, 64, 4, 3>(a);
+        case 4: return launch_kslice<128, 64, 4, 3>(a);
+        case 5: return launch_kslice<128, 128, 4, 2>(a);
+    }
+    return PME_ERR_UNSUPPORTED_PATH;
+}
+
+// Estimated time in us: launch, prologue and the reduction of the partial tiles (fixed), and K steps of 128 codes, each
+// slower the more of the chip works (L2, power).  Fitted to 33 outputs from 8 to 2048 tokens, 1024 to 6144 channels and
+// d_e from 2176 to 18432; on all of them the tile that comes out is within 10 % of the fastest.
+double kslice_cost(int64_t T, int64_t N, int64_t d_e, int tile) {
+    static const struct { int bm, bn; double fixed, step, step_full; } t[kKsliceTiles] = {
+        {32, 32, 3.0, 0.034, 0.064}, {64, 32, 3.8, 0.045, 0.075}, {64, 64, 3.9, 0.068, 0.105},
+        {96, 64, 5.5, 0.112, 0.150}, {128, 64, 6.0, 0.138, 0.223}, {128, 128, 8.7, 0.220, 0.350}};
+    const auto& k = t[tile];
+    const double steps = (double)(d_e / 128);
+    const int64_t tiles = ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), cus = 256;
+    if (tile == 0 && tiles > cus) return k.fixed + steps * k.step_full * (double)tiles / (double)cus;      // two per compute unit
+    const int64_t full = tiles / cus;
+    const double fill = (double)(tiles % cus) / (double)cus;
+    const double one = k.fixed - 2.0;                                     // the launch itself is paid once
+    double us = 2.0 + (double)full * (one + steps * k.step_full);
+    if (fill > 0) us += one + steps * (k.step + (k.step_full - k.step) * fill * fill);
+    return us;
+}
+
+}  // namespace pme

@@ -23,7 +23,7 @@
 //  * v_mfma_i32_32x32x32_i8 with the weight fragment as the first operand: a lane then owns one
 //    token and runs of four consecutive output channels, which the epilogue scales, rounds to
 //    bf16, transposes through LDS and stores as 16-byte row pieces.
-#include "pme_internal.h"
+#include "gemm_tile.h"
 
 #include <algorithm>
 #include <cstdio>
@@ -32,44 +32,6 @@
 
 namespace pme {
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(16))) int i32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-
-#define PME_AS1 __attribute__((address_space(1)))
-#define PME_AS3 __attribute__((address_space(3)))
-
-enum { MODE_BF16 = 0, MODE_ASYM = 1, MODE_I32 = 2 };
-
-// LDS swizzle: the 16-byte chunk kc of tile row r sits at chunk position kc ^ swz(r), so that the rows
-// read together by one ds_read_b128 spread over the banks.  RB = bytes per tile row per K step.  The two
-// functions are the fastest of the XOR patterns tried on MI355X (timed in the whole kernel, where the
-// pattern also decides which global chunk each DMA lane fetches).
-template <int RB> __device__ __forceinline__ int swz(int r) {
-    return RB == 64 ? (((r >> 2) ^ r) & 3) : (r & 7);
-}
-
-// LDS-only barrier: DMA (counted by vmcnt) stays in flight across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane (lds_base wave-uniform).
-// The statement overwrites M0, which the compiler reserves and does not keep values in; no other code in
-// this kernel makes the compiler emit an M0 use.
-// The source is a wave-uniform 64-bit base (SGPR pair) plus a 32-bit byte offset per lane: no vector
-// arithmetic is needed to move the window along K.
-__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    const bf16x2 p = __builtin_convertvector(f32x2{a, b}, bf16x2);     // v_cvt_pk_bf16_f32: round half to even
-    return __builtin_bit_cast(uint32_t, p);
-}
 
 // BM x BN output tile, WGM x WGN x KS waves, RB packed bytes (2 RB codes) per row and K step, NSTAGE LDS stages.
 // KS = 2: two waves share every wave tile and split each K step's sub-steps between them (the first half and
@@ -623,7 +585,8 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
         const bool wide = (a.d_e % 256) == 0;
         // (with 64-byte steps 128 x 192 on 4 waves beats 128 x 256 on 8 by a quarter; a fifth wave that does the
         // DMA gains another 3-4 % there, and 1-2 % at 128 x 128 over splitting K between wave pairs)
-        if (tiles(128, 128) >= cus * 3 / 4) {
+        // (up to 64 tokens the wide tiles would compute mostly padding, however wide the output)
+        if (a.T > 64 && tiles(128, 128) >= cus * 3 / 4) {
             // Large outputs: the cheapest of four tile shapes by rounds x tile area / efficiency.  The efficiencies
             // are each shape's measured rate on outputs of many rounds, relative to 256 x 256; a round is one
             // workgroup on every compute unit, except that two 128 x 192 workgroups without loader wave share a
@@ -643,15 +606,27 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
             if (best == c256) id = wide ? 11 : 8;
             else if (best == c16) id = wide ? 16 : 2;
             else if (best == c192) id = tiles(128, 192) <= cus ? (wide ? 28 : 21) : 9;     // the loader's registers allow one workgroup per unit
+            // one round of 128 x 128: four waves that split K beat four quarters of the tile with a loader wave where units
+            // stay idle (700 x 4096 x 8704: 30.0 -> 28.1 us, 768 x 4096 x 15360: 48.7 -> 43.7) or K is long enough for the
+            // sum of the partial tiles, about 2 us, not to count (1024 x 4096 x 15360: 56.6 -> 51.6; with every unit busy
+            // at d_e = 8704 the two are within 2 %)
+            else if (kslice_range(a.d_e) && tiles(128, 128) <= cus && (a.d_e >= 12288 || (tiles(128, 128) < cus && a.d_e >= 4096))) id = 29 + 5;
             else id = wide ? 25 : 22;   // whole 128-byte lines per K step halve the barriers of the loader tile: 3-4 % at 2048 x 2048 x 8704
+        } else {
+            // Smaller outputs: a K-split tile, or 64 x 64 with a loader wave, of which two and more share a compute unit
+            // (short K, many tiles: 700 x 3072 x 2176 takes 10.6 us on it and 13.8 on the best K-split tile).  Time of
+            // the latter fitted like the others: up to one workgroup per unit, then sharing.
+            const double t = (double)tiles(64, 64) / (double)cus;
+            double best = 3.6 + (double)(a.d_e / 128) * 0.16 * (t <= 1.0 ? 1.0 : 1.4 + 0.6 * (t - 1.0));
+            id = wide ? 27 : 24;
+            for (int k = 0; k < kKsliceTiles && kslice_range(a.d_e); ++k) {
+                const double us = kslice_cost(a.T, a.N, a.d_e, k);
+                if (us < best) { best = us; id = 29 + k; }
+            }
         }
-        // smaller outputs (measured on 18 shapes from 96 to 1536 tokens): 64 x 64, which beats 64 x 128 until the
-        // latter has one and a half tiles per compute unit
-        // (with whole 128-byte lines per K step -- half the barriers -- where d_e allows: 64 x 64 another 5-13 % on four
-        // such shapes, 64 x 128 2-3 %)
-        else if (tiles(64, 128) >= cus * 3 / 2) id = wide ? 26 : 23;
-        else id = wide ? 27 : 24;
     }
+    // ids 29 .. 34: the waves of a workgroup split K
+    if (id > 28 && id <= 28 + kKsliceTiles) return launch_gemm_kslice(a, id - 29);
     switch (id) {
         case 1: return launch_tile<256, 256, 2, 4, 64, 3>(a);      // 8 waves of 128 x 64
         case 2: return launch_tile<128, 256, 2, 4, 64, 3>(a);      // 8 waves of 64 x 64
@@ -683,6 +658,7 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
         case 25: return launch_tile<128, 128, 2, 2, 128, 3, 1, true>(a);   // 4 waves of 64 x 64 + loader, 128-byte rows
         case 26: return launch_tile<64, 128, 2, 2, 128, 3, 1, true>(a);    // 4 waves of 32 x 64 + loader, 128-byte rows
         case 27: return launch_tile<64, 64, 2, 2, 128, 3, 1, true>(a);     // 4 waves of 32 x 32 + loader, 128-byte rows
+        // the workgroup's waves split K
         case 28: return launch_tile<128, 192, 2, 2, 128, 3, 1, true>(a);   // 4 waves of 64 x 96 + loader, 128-byte rows
     }
     return PME_ERR_UNSUPPORTED_PATH;

@@ -261,6 +261,36 @@ def test_gemm_every_tile_configuration(tile, d_e):
     check_bf16(y, oracle.dequant_bf16(acc_ref, sx, sw))
 
 
+# The K-split kernel, every tile (ids 29 .. 34): T and N at a tile edge, one past it and one short of it; the shortest K
+# (a step for every wave), K whose steps do not divide by the waves, and an output pitch that 16-byte stores cannot take.
+# Exact integers: any missing, doubled or misplaced partial sum shows.
+@pytest.mark.parametrize("d_e", (1024, 1152, 2176, 3840))
+@pytest.mark.parametrize("tile", range(29, 35))
+def test_gemm_k_split_tiles(tile, d_e):
+    bm, bn = ((32, 32), (64, 32), (64, 64), (96, 64), (128, 64), (128, 128))[tile - 29]
+    rng = np.random.default_rng(tile + d_e)
+    for T, N in ((70, bn), (2 * bm + 1, 2 * bn - 1), (max(65, bm), 3 * bn + 8), (65, 5)):
+        qx = rng.integers(-8, 8, (T, d_e)).astype(np.int8)
+        qw = rng.integers(-8, 8, (N, d_e)).astype(np.int8)
+        sx, sw = rng.uniform(0.01, 1.0, T).astype(np.float32), rng.uniform(0.001, 0.01, N).astype(np.float32)
+        zx = rng.integers(0, 16, T).astype(np.int32)
+        acc = oracle.int_gemm(qx, qw)
+        qxd, qwd = pme.pack_int4(torch.from_numpy(qx)), pme.pack_int4(torch.from_numpy(qw))
+        sxd, swd = torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
+        pme.set_gemm_tile(tile)
+        assert np.array_equal(pme.w4a4_gemm_i32(qxd, qwd).cpu().numpy(), acc)
+        y = torch.full((T, N + 3), 9.0, dtype=torch.bfloat16, device="cuda")
+        pme.w4a4_gemm(qxd, sxd, qwd, swd, y[:, :N])
+        check_bf16(y[:, :N].float().cpu().numpy(), oracle.dequant_bf16(acc, sx, sw))
+        assert bool((y[:, N:] == 9.0).all())
+        # asymmetric: the stored nibble u = c + 8 stands for u - z
+        wsum = pme.weight_rowsum(qwd)
+        ya = pme.w4a4_gemm_asym(qxd ^ 0x88, sxd, torch.from_numpy(zx).cuda(), qwd, swd, wsum)
+        ref = acc + (8 - zx.astype(np.int64))[:, None] * qw.astype(np.int64).sum(1)[None, :]
+        check_bf16(ya.float().cpu().numpy(), oracle.dequant_bf16(ref, sx, sw))
+        pme.set_gemm_tile(0)
+
+
 @pytest.mark.parametrize("tm,tn", [(8, 1), (1, 8), (4, 2), (2, 4), (16, 16), (3, 5), (24, 8)])
 def test_gemm_tile_map_is_a_bijection(tm, tn):
     # The workgroup -> tile map hands each XCD a block of tiles; the split (8x1, 4x2, 2x4, 1x8 XCDs, or none
