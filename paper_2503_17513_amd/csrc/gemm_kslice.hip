@@ -351,23 +351,19 @@ pme_status launch_gemm_kslice(const GemmArgs& a, int tile) {
     return PME_ERR_UNSUPPORTED_PATH;
 }
 
-// Estimated time in us: launch, prologue and the reduction of the partial tiles (fixed), and K steps of 128 codes, each
-// slower the more of the chip works (L2, power).  Fitted to 33 outputs from 8 to 2048 tokens, 1024 to 6144 channels and
-// d_e from 2176 to 18432; on all of them the tile that comes out is within 10 % of the fastest.
+// Estimated time in us of a single round of workgroups: launch, prologue and the sum of the partial tiles (fixed), and K
+// steps of 128 codes, each slower the more of the chip works (L2, power).  Fitted to 33 outputs from 8 to 2048 tokens,
+// 512 to 6144 channels and d_e from 2176 to 22016.  A second round pays the fixed part again and loses to the tiled kernel
+// (647 x 2834 x 9728: 33.5 us on two rounds of 64 x 64, 26.9 there; 1616 x 1152 x 15360: 42.8 and 37.3), so it is refused
+// with an infinite estimate; 32 x 32 shares its compute units instead.
 double kslice_cost(int64_t T, int64_t N, int64_t d_e, int tile) {
     static const struct { int bm, bn; double fixed, step, step_full; } t[kKsliceTiles] = {
-        {32, 32, 3.0, 0.034, 0.064}, {64, 32, 3.8, 0.045, 0.075}, {64, 64, 3.9, 0.068, 0.105},
-        {96, 64, 5.5, 0.112, 0.150}, {128, 64, 6.0, 0.138, 0.223}, {128, 128, 8.7, 0.220, 0.350}};
+        {32, 32, 3.0, 0.034, 0.064}, {64, 32, 3.8, 0.045, 0.095}, {64, 64, 3.9, 0.068, 0.160},
+        {96, 64, 5.5, 0.112, 0.180}, {128, 64, 6.0, 0.138, 0.223}, {128, 128, 8.7, 0.220, 0.350}};
     const auto& k = t[tile];
-    const double steps = (double)(d_e / 128);
-    const int64_t tiles = ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), cus = 256;
-    if (tile == 0 && tiles > cus) return k.fixed + steps * k.step_full * (double)tiles / (double)cus;      // two per compute unit
-    const int64_t full = tiles / cus;
-    const double fill = (double)(tiles % cus) / (double)cus;
-    const double one = k.fixed - 2.0;                                     // the launch itself is paid once
-    double us = 2.0 + (double)full * (one + steps * k.step_full);
-    if (fill > 0) us += one + steps * (k.step + (k.step_full - k.step) * fill * fill);
-    return us;
+    const double steps = (double)(d_e / 128), fill = (double)(((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn)) / 256.0;
+    if (fill > 1.0) return tile == 0 ? k.fixed + steps * k.step_full * fill : 1e30;
+    return k.fixed + steps * (k.step + (k.step_full - k.step) * fill * fill);
 }
 
 }  // namespace pme

@@ -760,7 +760,12 @@ pme_status launch_out(const RotateArgs& a, int ks, int nwaves) {
     const int rows = (int)((a.d + L::NC - 1) >> KLOG2);
     pme_status st = PME_OK;
     const Fragment* ptable = fragment_table(a.b >> a.fold, a.fold, rows, a.stream, &st);
-    if (!ptable) return st;
+    if (!ptable) {
+        // fp32 tokens whose planes would not all fit in LDS with the fragments (orders 312 and 344; 512 columns and more
+        // than one K step) may be captured cold: the plain kernel, which needs no table, takes them then
+        if (F32IN && st == PME_ERR_COLD_SHAPE && (size_t)(NS * L::MT + nwaves * TPW) * ks * 1024 > kMaxDynLds) return PME_ERR_UNSUPPORTED_PATH;
+        return st;
+    }
     auto kern = k_rotate_mfma<KLOG2, TPW, F32IN, OUT, false, BGLOBAL, KSREG>;
     // the same kernel runs with different LDS sizes (they follow the shape): allow the largest one accepted above
     static std::atomic<uint32_t> done;
