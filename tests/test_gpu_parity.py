@@ -716,6 +716,29 @@ def test_first_use_of_a_shape_under_graph_capture_is_refused_and_the_capture_sur
     assert torch.equal(qx, want_q) and torch.equal(sx, want_s)
 
 
+def test_fp32_rows_of_the_largest_blocks_are_captured_cold():
+    # order 312 from fp32: the matrix-core kernel needs a table that a capture cannot fill, so the plain kernel is captured
+    d, d_e, T = 13000, 19968, 3                     # 204 real base rows: no other test uses them
+    x = _acts(T, d, d_e, "f32", seed=3)
+    xd = to_device(x, "f32")
+    pme.hadamard_expand_quant(xd[:, :12000], d_e)   # (another table; loads the library)
+    qx = torch.zeros((T, d_e // 2), dtype=torch.uint8, device="cuda")
+    sx = torch.zeros((T,), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        pme.hadamard_expand_quant(xd, d_e, qx, sx)
+    ref = oracle.rotate_structured(x, d_e)
+    q_ref, s_ref = oracle.quantize_sym_int4(ref)
+    for _ in range(3):
+        qx.zero_()
+        sx.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        check_scales(sx.cpu().numpy(), s_ref)
+        check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
+
+
 def test_probe_mfma():
     # every accumulator grows by the same amount per instruction: the checksum is linear in iters
     out = torch.zeros(512 * 256, dtype=torch.int32, device="cuda")
