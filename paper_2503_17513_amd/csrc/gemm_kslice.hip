@@ -13,6 +13,7 @@
 #include "gemm_tile.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <string>
 
@@ -351,19 +352,58 @@ pme_status launch_gemm_kslice(const GemmArgs& a, int tile) {
     return PME_ERR_UNSUPPORTED_PATH;
 }
 
-// Estimated time in us of a single round of workgroups: launch, prologue and the sum of the partial tiles (fixed), and K
-// steps of 128 codes, each slower the more of the chip works (L2, power).  Fitted to 33 outputs from 8 to 2048 tokens,
-// 512 to 6144 channels and d_e from 2176 to 22016.  A second round pays the fixed part again and loses to the tiled kernel
-// (647 x 2834 x 9728: 33.5 us on two rounds of 64 x 64, 26.9 there; 1616 x 1152 x 15360: 42.8 and 37.3), so it is refused
-// with an infinite estimate; 32 x 32 shares its compute units instead.
+// Estimated times in us of the three kernels for outputs of less than a chip of large tiles, K in steps of 128 codes.  Fitted
+// to 4500 outputs of 1 .. 2048 tokens, 320 .. 28672 channels and d_e 1024 .. 32768, each timed with three weight matrices in
+// turn (in the caches) and with 600 MB of them in turn (from memory); the estimate is of the geometric mean of the two, good
+// to 4-10 % for the K-split tiles and 5 % for the others.  Weights that come from memory slow the K-split kernel most (64-byte
+// rows, a ring of two or three steps: 16 x 2048 x 8704 takes 6.6 us warm and 9.5 cold, the streaming kernel 8.0 and 7.8).
+
+// K-split tile: one round of workgroups; the 32 x 32 one, of which two share a compute unit, also several.  A second round of
+// the others pays prologue and sum again and loses to the tiled kernel (647 x 2834 x 9728: 33.5 us on two rounds of 64 x 64, 26.9
+// there; 1616 x 1152 x 15360: 42.8 and 37.3).
 double kslice_cost(int64_t T, int64_t N, int64_t d_e, int tile) {
-    static const struct { int bm, bn; double fixed, step, step_full; } t[kKsliceTiles] = {
-        {32, 32, 3.0, 0.034, 0.064}, {64, 32, 3.8, 0.045, 0.095}, {64, 64, 3.9, 0.068, 0.160},
-        {96, 64, 5.5, 0.112, 0.180}, {128, 64, 6.0, 0.138, 0.223}, {128, 128, 8.7, 0.220, 0.350}};
+    static const struct { int bm, bn; double fixed, step, by_fill, by_rows; } t[kKsliceTiles] = {
+        {32, 32, 3.15, 0.0576, 0.0344, 0.0378}, {64, 32, 3.84, 0.0713, 0.0201, 0.0534}, {64, 64, 4.16, 0.1062, 0.0250, 0.0865},
+        {96, 64, 5.16, 0.1512, 0.0330, 0.1135}, {128, 64, 5.72, 0.1720, 0.0441, 0.0957}, {128, 128, 9.13, 0.2447, 0.0759, 0.1588}};
     const auto& k = t[tile];
-    const double steps = (double)(d_e / 128), fill = (double)(((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn)) / 256.0;
-    if (fill > 1.0) return tile == 0 ? k.fixed + steps * k.step_full * fill : 1e30;
-    return k.fixed + steps * (k.step + (k.step_full - k.step) * fill * fill);
+    const double steps = (double)(d_e / 128), rows = (double)((N + k.bn - 1) / k.bn) / 256.0;
+    const double fill = (double)((T + k.bm - 1) / k.bm) * rows;
+    // 4.3: the largest that was timed; below d_e = 2048 only the 32 x 32 tile gains, and only on a single round (768 x 1024 x 1024:
+    // 6.5 us on three of them to a unit, 5.2 tiled)
+    if (fill > (tile == 0 && d_e >= 2048 ? 4.3 : 1.0) || (tile > 0 && d_e < 2048)) return 1e30;
+    if (tile == 0) {
+        const double more = std::max(0.0, fill - 1.0), rounds = std::ceil(fill) - 1.0, tokens = (double)std::min<int64_t>(T, 32) / 32.0;
+        return k.fixed + 0.64 * more + steps * (k.step + 0.0306 * rounds + k.by_fill * more + (k.by_rows + 0.0355 * tokens) * rows);
+    }
+    return k.fixed + steps * (k.step + k.by_fill * fill + k.by_rows * rows);
+}
+
+// The weight-streaming kernel: rounds of 4096 channels, one workgroup per compute unit.
+double decode_cost(int64_t T, int64_t N, int64_t d_e) {
+    const double steps = (double)(d_e / 128), rounds = (double)((N + 4095) / 4096);
+    return 2.59 + steps * (rounds * (0.0386 + 0.0022 * (double)T) + 0.0179 * (double)N / 4096.0);
+}
+
+// 64 x 64 tiles with a loader wave, of which two and more share a compute unit.
+double loader64_cost(int64_t T, int64_t N, int64_t d_e) {
+    const double steps = (double)(d_e / 128), fill = (double)(((T + 63) / 64) * ((N + 63) / 64)) / 256.0;
+    const double rounds = std::ceil(fill) - 1.0;
+    return 3.76 + 0.74 * rounds + steps * (0.1616 + 0.0250 * std::min(fill, 1.0) + 0.0882 * std::max(fill - 1.0, 0.0) + 0.0381 * rounds);
+}
+
+// The K-split tile that is estimated to beat `other` us by more than 4 %, or -1.  Its time over that of the kernel it replaces,
+// on the 3900 fitted outputs of up to 6144 channels: from the caches 0.92 in the mean up to 16 tokens, 0.61 up to 64 and 0.72
+// above, beyond 1.03 on 30 outputs; from memory 0.98, 0.82 and 0.79, beyond 1.03 on one output in ten (mostly 12 .. 32 tokens
+// by less than 2048 channels, 20 % at most, where it gains 30 % from the caches).
+int kslice_choice(int64_t T, int64_t N, int64_t d_e, double other) {
+    if (!kslice_range(d_e)) return -1;
+    double best = 0.96 * other;
+    int tile = -1;
+    for (int k = 0; k < kKsliceTiles; ++k) {
+        const double us = kslice_cost(T, N, d_e, k);
+        if (us < best) { best = us; tile = k; }
+    }
+    return tile;
 }
 
 }  // namespace pme

@@ -607,22 +607,18 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
             else if (best == c16) id = wide ? 16 : 2;
             else if (best == c192) id = tiles(128, 192) <= cus ? (wide ? 28 : 21) : 9;     // the loader's registers allow one workgroup per unit
             // one round of 128 x 128: four waves that split K beat four quarters of the tile with a loader wave where units
-            // stay idle (700 x 4096 x 8704: 30.0 -> 28.1 us, 768 x 4096 x 15360: 48.7 -> 43.7) or K is long enough for the
-            // sum of the partial tiles, about 2 us, not to count (1024 x 4096 x 15360: 56.6 -> 51.6; with every unit busy
-            // at d_e = 8704 the two are within 2 %)
-            else if (kslice_range(a.d_e) && tiles(128, 128) <= cus && (a.d_e >= 12288 || (tiles(128, 128) < cus && a.d_e >= 4096))) id = 29 + 5;
+            // stay idle (us from the caches / from memory: 700 x 4096 x 8704 32.6 / 33.3 and 29.8 / 31.4; at d_e = 4352 they lose
+            // 2 / 6 %) or K is long enough for the sum of the partial tiles, about 2 us, not to count (1024 x 4096 x 15360
+            // 58.4 / 59.6 and 51.2 / 53.0); not for one row of tiles, where no two workgroups share weights (128 x 28672 x
+            // 8704: 13 / 16 % slower)
+            else if (kslice_range(a.d_e) && a.T > 128 && tiles(128, 128) <= cus &&
+                     (a.d_e >= 12288 || (tiles(128, 128) < cus && a.d_e >= 8192))) id = 29 + 5;
             else id = wide ? 25 : 22;   // whole 128-byte lines per K step halve the barriers of the loader tile: 3-4 % at 2048 x 2048 x 8704
         } else {
-            // Smaller outputs: a K-split tile, or 64 x 64 with a loader wave, of which two and more share a compute unit
-            // (short K, many tiles: 700 x 3072 x 2176 takes 10.6 us on it and 13.8 on the best K-split tile).  Time of
-            // the latter fitted like the others: up to one workgroup per unit, then sharing.
-            const double t = (double)tiles(64, 64) / (double)cus;
-            double best = 3.6 + (double)(a.d_e / 128) * 0.16 * (t <= 1.0 ? 1.0 : 1.4 + 0.6 * (t - 1.0));
-            id = wide ? 27 : 24;
-            for (int k = 0; k < kKsliceTiles && kslice_range(a.d_e); ++k) {
-                const double us = kslice_cost(a.T, a.N, a.d_e, k);
-                if (us < best) { best = us; id = 29 + k; }
-            }
+            // Smaller outputs: a K-split tile, or 64 x 64 with a loader wave (short K, many tiles: 700 x 3072 x 2176 takes
+            // 10.6 us on it and 13.8 on the best K-split tile), with whole 128-byte lines per K step where d_e allows.
+            const int k = kslice_choice(a.T, a.N, a.d_e, loader64_cost(a.T, a.N, a.d_e));
+            id = k >= 0 ? 29 + k : wide ? 27 : 24;
         }
     }
     // ids 29 .. 34: the waves of a workgroup split K
@@ -658,7 +654,6 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
         case 25: return launch_tile<128, 128, 2, 2, 128, 3, 1, true>(a);   // 4 waves of 64 x 64 + loader, 128-byte rows
         case 26: return launch_tile<64, 128, 2, 2, 128, 3, 1, true>(a);    // 4 waves of 32 x 64 + loader, 128-byte rows
         case 27: return launch_tile<64, 64, 2, 2, 128, 3, 1, true>(a);     // 4 waves of 32 x 32 + loader, 128-byte rows
-        // the workgroup's waves split K
         case 28: return launch_tile<128, 192, 2, 2, 128, 3, 1, true>(a);   // 4 waves of 64 x 96 + loader, 128-byte rows
     }
     return PME_ERR_UNSUPPORTED_PATH;

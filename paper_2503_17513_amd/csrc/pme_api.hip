@@ -91,13 +91,12 @@ int64_t max_slice_rows(int64_t row_bytes) { return std::max<int64_t>(256, (((int
 pme_status run_gemm_slice(const pme::GemmArgs& a) {
     int path = g_path.load();
     if (path != PME_PATH_GENERIC) {
-        // a handful of tokens: the weight-streaming kernel where its fixed cost, without rings and partial tiles to add,
-        // outweighs that it reads the codes of all tokens once per 16 channels (us, streaming / 32 x 32 tiles splitting K:
-        // 1 x 2048 x 8448 4.8 / 5.3, 8 x 3072 x 2176 2.9 / 3.8; 16 x 4096 x 15360 12.0 / 7.8, 16 x 6144 x 8704 12.9 / 5.5, 4 x 6144 x 8704 9.1 / 5.5, 8 x 4096 x 8704 6.6 / 5.4)
-        // outside the K-split kernel's measured range of d_e: up to 64 tokens while the output has fewer than 128 tiles of 64 x 64
-        const bool stream_weights = pme::kslice_range(a.d_e)
-            ? a.T <= 16 && (a.d_e <= 4096 || (a.T <= 2 && a.d_e < 12288 && a.N * a.d_e <= (36 << 20)) || (a.T <= 8 && a.N * a.d_e <= (18 << 20)))
-            : a.T <= 16 || (a.T <= 64 && a.N < 8192);
+        // few tokens: the weight-streaming kernel while the output has fewer than 128 tiles of 64 x 64, unless a K-split tile
+        // is estimated faster: from two rounds of 4096 channels on and with more tokens, whose codes the streaming kernel
+        // reads once per 16 channels (us from the caches / from memory, streaming and K-split: 1 x 4096 x 12288 8.2 / 8.0 and
+        // 9.8 / 11.9, 1 x 5120 x 12288 13.3 / 13.0 and 9.8 / 12.3, 32 x 4096 x 15360 18.8 / 19.2 and 13.6 / 18.2)
+        const bool stream_weights = (a.T <= 16 || (a.T <= 64 && a.N < 8192)) &&
+                                    pme::kslice_choice(a.T, a.N, a.d_e, pme::decode_cost(a.T, a.N, a.d_e)) < 0;
         pme_status s = stream_weights ? pme::launch_gemm_decode(a) : pme::launch_gemm_mfma(a);
         if (s == PME_ERR_UNSUPPORTED_PATH && stream_weights && a.T > 16) s = pme::launch_gemm_mfma(a);
         if (s != PME_ERR_UNSUPPORTED_PATH || path == PME_PATH_MFMA) return s;

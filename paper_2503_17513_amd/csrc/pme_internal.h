@@ -64,11 +64,13 @@ pme_status launch_gemm_generic(const GemmArgs& a);
 pme_status launch_gemm_mfma(const GemmArgs& a);
 pme_status launch_gemm_decode(const GemmArgs& a);
 // the K-split kernel: tiles 0 .. kKsliceTiles - 1 (32 x 32, 64 x 32, 64 x 64, 96 x 64, 128 x 64, 128 x 128).  It takes d_e of
-// 1024 and more; the automatic choice uses it where its time was measured (2176 .. 22016) and somewhat beyond.
+// 1024 and more; the automatic choice uses it where it was timed (1024 .. 32768).
 constexpr int kKsliceTiles = 6;
 inline bool kslice_range(int64_t d_e) { return d_e >= 1024 && d_e <= 32768; }
 pme_status launch_gemm_kslice(const GemmArgs& a, int tile);
-double kslice_cost(int64_t T, int64_t N, int64_t d_e, int tile);      // estimated us
+double decode_cost(int64_t T, int64_t N, int64_t d_e);                // estimated us
+double loader64_cost(int64_t T, int64_t N, int64_t d_e);
+int kslice_choice(int64_t T, int64_t N, int64_t d_e, double other);   // tile, or -1: not faster than `other` us
 pme_status launch_weight_rowsum(const uint8_t* qw, int64_t N, int64_t d_e, int32_t* wsum, hipStream_t s);
 pme_status launch_pack_int4(const int8_t* codes, int64_t pairs, uint8_t* packed, hipStream_t s);
 pme_status launch_probe_copy(const void* src, void* dst, size_t bytes, hipStream_t s);

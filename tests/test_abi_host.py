@@ -227,6 +227,34 @@ def test_gemm_plan_names_the_kernel_without_launching():
         pme.set_path(pme.PATH_AUTO)
 
 
+# (T, d_e, N) and the int4 kernel that measured faster, in us from the caches / from memory
+PLANS = [
+    # few tokens by up to 4096 channels: the streaming kernel at any K (1 x 12288 x 2048: 7.6 / 7.2, K-split 9.2 / 11.2;
+    # 2 x 15360 x 3072: 9.5 / 9.3, 10.7 / 13.8; 1 x 32768 x 2048: 14.6 / 14.4, 17.2 / 24.0)
+    (1, 8448, 2048, "k_gemm_decode"), (8, 8448, 2048, "k_gemm_decode"), (4, 8704, 4096, "k_gemm_decode"),
+    (1, 12288, 2048, "k_gemm_decode"), (2, 12288, 2112, "k_gemm_decode"), (3, 15360, 1356, "k_gemm_decode"),
+    (2, 15360, 3072, "k_gemm_decode"), (1, 22016, 3072, "k_gemm_decode"), (1, 32768, 2048, "k_gemm_decode"),
+    (16, 1024, 3072, "k_gemm_decode"), (58, 1024, 5056, "k_gemm_decode"),
+    # from a second round of 4096 channels, or with more tokens, a K-split tile (1 x 12288 x 5120: 9.8 / 12.3, streaming 13.3 / 13.0;
+    # 32 x 15360 x 4096: 13.6 / 18.2, 18.8 / 19.2)
+    (1, 12288, 5120, "k_gemm_kslice<32, 32, 8, 2, 0>"), (4, 8704, 6144, "k_gemm_kslice<32, 32, 8, 2, 0>"),
+    (32, 15360, 4096, "k_gemm_kslice<32, 32, 8, 2, 0>"), (48, 8704, 6144, "k_gemm_kslice<64, 32, 8, 3, 0>"),
+    # small outputs: each K-split tile, and the 64 x 64 tile where K is short or the tiles many
+    (333, 9728, 2048, "k_gemm_kslice<64, 64, 8, 2, 0>"), (517, 8704, 2048, "k_gemm_kslice<96, 64, 4, 3, 0>"),
+    (900, 15360, 2048, "k_gemm_kslice<128, 64, 4, 3, 0>"), (768, 15360, 4096, "k_gemm_kslice<128, 128, 4, 2, 0>"),
+    (64, 1024, 14336, "k_gemm_mfma<64, 64, "), (768, 1024, 1024, "k_gemm_mfma<64, 64, "), (700, 2176, 3072, "k_gemm_mfma<64, 64, "),
+    (32, 15360, 28672, "k_gemm_mfma<64, 64, "),
+    # one round of 128 x 128: not split while K is short, nor for a single row of tiles (128 x 8704 x 28672: 13 / 16 % slower split)
+    (700, 4352, 4096, "k_gemm_mfma<128, 128, "), (128, 8704, 28672, "k_gemm_mfma<128, 128, "),
+]
+
+
+@pytest.mark.parametrize("T,d_e,N,kernel", PLANS)
+def test_gemm_plan_takes_the_faster_kernel(T, d_e, N, kernel):
+    assert pme.gemm_plan(T, d_e, N).startswith(kernel)
+    assert pme.gemm_plan(T, d_e, N, variant=1).startswith(kernel.replace(", 0>", ", 1>"))
+
+
 def test_pack_int4_argument_errors():
     f = pme.lib().pme_pack_int4
     assert f(None, 4, 8, FAKE, None) == NULL
