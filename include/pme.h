@@ -24,7 +24,9 @@
  *    table of base-block fragments in library-owned device memory (a static pool of 16 MB per device, 7 to
  *    154 KB per shape, kept for the life of the process) and waits for that small kernel once; run a shape
  *    once before capturing it in a HIP graph (under capture such a first call returns PME_ERR_COLD_SHAPE
- *    and enqueues nothing).
+ *    and enqueues nothing; fp32 rows of orders 312 and 344 with fewer than 512 tokens, and fp32 rows of more
+ *    values than the kernel's LDS holds at once, are captured on the plain-ALU kernel then, which needs no
+ *    table).
  *  - Arguments are validated on the host before any HIP call.  A status other than
  *    PME_OK means nothing was launched (PME_ERR_HIP excepted: a launch was refused by
  *    the runtime); the fused pme_expanded_linear* calls ask both of their stages whether a

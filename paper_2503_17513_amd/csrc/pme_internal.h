@@ -23,6 +23,7 @@ struct RotateArgs {
     hipStream_t stream;
     int fold = 0;        // set by the MFMA launcher: butterfly stages folded into the base block (then b, k describe the folded shape)
     bool dry = false;    // only answer whether a kernel takes the shape: nothing is launched, no table is built
+    bool plain_if_cold = false;   // set by the MFMA launcher: a cold capture of this shape runs on the plain kernel
 };
 
 struct MxGemmArgs {

@@ -761,9 +761,7 @@ pme_status launch_out(const RotateArgs& a, int ks, int nwaves) {
     pme_status st = PME_OK;
     const Fragment* ptable = fragment_table(a.b >> a.fold, a.fold, rows, a.stream, &st);
     if (!ptable) {
-        // fp32 tokens whose planes would not all fit in LDS with the fragments (orders 312 and 344; 512 columns and more
-        // than one K step) may be captured cold: the plain kernel, which needs no table, takes them then
-        if (F32IN && st == PME_ERR_COLD_SHAPE && (size_t)(NS * L::MT + nwaves * TPW) * ks * 1024 > kMaxDynLds) return PME_ERR_UNSUPPORTED_PATH;
+        if (st == PME_ERR_COLD_SHAPE && a.plain_if_cold) return PME_ERR_UNSUPPORTED_PATH;
         return st;
     }
     auto kern = k_rotate_mfma<KLOG2, TPW, F32IN, OUT, false, BGLOBAL, KSREG>;
@@ -882,6 +880,13 @@ pme_status launch_rotate_mfma(const RotateArgs& in) {
     }
     // few tokens: spread a token over as many waves as it has tiles
     if (a.T < 512 && a.k <= 8) tpw = 1;
+    // fp32 rows of the largest blocks, which the plain kernel, that needs no table, takes when they are captured cold: those of
+    // more than ten tiles (orders 312 and 344) with few tokens, and those whose term planes would not fit in LDS at once.  All
+    // other shapes are refused there.
+    if (f32) {
+        const int nw = (nt + tpw - 1) / tpw, most = (tpw == 1 && a.k <= 8) || a.k == 6 ? kMaxWaves : kMaxWaves / 2;
+        a.plain_if_cold = nw > most || (3 * (nc / 16) + nw * tpw) * ks > 159;      // KB
+    }
     if (g_tpw_override > 0) tpw = g_tpw_override;
     // P fragments read from the table in device memory instead of LDS:
     //  * 2^k = 64 with 8 tiles or more (orders 132 .. 152: 8448, 8960, 9728): staging nt ks KB of fragments

@@ -739,6 +739,47 @@ def test_fp32_rows_of_the_largest_blocks_are_captured_cold():
         check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
 
 
+# Base-row counts that no other test uses, so that the tables are cold.  Few tokens of order 312 and 344 have more tiles than a
+# workgroup has waves at one tile each, whatever the number of K steps; 132 x 256 has planes that do not fit at once.
+@pytest.mark.parametrize("T,d,d_e", [(3, 7000, 19968), (4, 5001, 19968), (3, 8100, 22016), (2, 13500, 22016), (2, 30100, 33792)])
+def test_fp32_shapes_captured_cold_run_on_the_plain_kernel(T, d, d_e):
+    x = _acts(T, d, d_e, "f32", seed=d)
+    xd = to_device(x, "f32")
+    qx = torch.zeros((T, d_e // 2), dtype=torch.uint8, device="cuda")
+    sx = torch.zeros((T,), dtype=torch.float32, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        pme.hadamard_expand_quant(xd, d_e, qx, sx)
+    ref = oracle.rotate_structured(x, d_e)
+    q_ref, s_ref = oracle.quantize_sym_int4(ref)
+    for _ in range(3):
+        qx.zero_()
+        sx.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        check_scales(sx.cpu().numpy(), s_ref)
+        check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
+
+
+@pytest.mark.parametrize("T,d,d_e", [(5, 6800, 8704), (600, 6500, 19968)])
+def test_fp32_shapes_that_a_cold_capture_refuses(T, d, d_e):
+    x = torch.ones((T, d), device="cuda")
+    marker = torch.zeros(8, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    status = None
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        marker.add_(1.0)
+        try:
+            pme.hadamard_expand_quant(x, d_e)
+        except pme.PmeError as e:
+            status = e.status
+    assert status == 9
+    g.replay()
+    torch.cuda.synchronize()
+    assert float(marker[0]) == 1.0
+
+
 def test_probe_mfma():
     # every accumulator grows by the same amount per instruction: the checksum is linear in iters
     out = torch.zeros(512 * 256, dtype=torch.int32, device="cuda")
