@@ -280,11 +280,11 @@ template <int KLOG2, int TPW> constexpr int max_waves() {
     return ((TPW == 1 && KLOG2 <= 8) || KLOG2 == 6) ? kMaxWaves : kMaxWaves / 2;
 }
 
-// fp32 input: K steps of the base block whose three bf16 term planes are in LDS at a time -- 48 KB of planes at 2^k = 64 ..
-// 256, so that three workgroups share a compute unit -- and the 4-column x 8-row units of the following ones that each
-// thread fetches ahead into registers (one unit a thread covers them with 4 waves; 32 registers a unit).
-template <int KLOG2> constexpr int f32_ksteps() { return KLOG2 == 6 ? 4 : KLOG2 <= 7 ? 2 : 1; }
-template <int KLOG2> constexpr int f32_ahead() { return KLOG2 == 9 ? 2 : 1; }
+// fp32 input: most K steps of the base block whose three bf16 term planes are in LDS at a time -- 48 KB of planes up to 2^k =
+// 256, so that three workgroups of up to four waves share a compute unit; up to 96 KB for few tokens at 2^k = 64 (one tile per
+// wave), where a second phase is a second trip to memory in a chain of latencies (8 x 9728 from 9120 values: 8.1 us, 7.5 with
+// a single phase).
+template <int KLOG2, int TPW> constexpr int f32_ksteps() { return KLOG2 == 6 && TPW == 1 ? 8 : KLOG2 <= 8 ? 256 >> KLOG2 : 1; }
 
 enum { OUT_SYM = 0, OUT_ASYM = 1, OUT_XHAT = 2, OUT_MXFP4 = 3 };   // int4 symmetric / asymmetric codes, fp32 values, MXFP4
 
@@ -304,8 +304,8 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     using L = Layout<KLOG2>;
     constexpr int NC = L::NC, MT = L::MT, NREG = L::NREG;
     constexpr int NS = F32IN ? 3 : 1;
-    constexpr int KG = f32_ksteps<KLOG2>();
-    const int plane_bytes = (F32IN ? KG : ks_count) * MT * 1024;     // one bf16 copy of the K-padded token (fp32: of KG K steps)
+    constexpr int KG = f32_ksteps<KLOG2, TPW>();
+    const int plane_bytes = (F32IN ? min(KG, ks_count) : ks_count) * MT * 1024;     // one bf16 copy of the K-padded token (fp32: of KG K steps)
 
     extern __shared__ __align__(1024) unsigned char smem[];   // NS token planes, then the B fragments
     __shared__ float red[2 * kRedSlots];
@@ -363,32 +363,37 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     // column c = 16 mt + c % 16.  What bounds this path is the chain load -> split -> LDS -> matrix cores, so the loads
     // of the next K steps (or token) are issued as soon as the registers of the current ones are split, and fly under
     // the matrix, FWHT and quantize phases; with only KG K steps of planes, several workgroups share a compute unit.
-    // (4096 rows of 14336 -> 15360, 266 MB: 178 us with the whole token's planes, 96 KB, filled without prefetch and one
-    // workgroup per compute unit, 70 us so.)
-    // A unit is 4 columns x 8 rows: 16-byte loads, and the four 16-byte stores of a lane go to slots whose low bits are
-    // XORed with mt so that the 16 slots of a bank round are all different.
-    constexpr int AHEAD = f32_ahead<KLOG2>(), UNITS = KG * NC, UPR = NC / 4;      // units of a phase; units per 8-row group
-    f32x4 ahead[F32IN ? AHEAD : 1][8];
-    const bool vec4 = F32IN && (reinterpret_cast<uintptr_t>(xv) & 15) == 0 && (ldx & 3) == 0 && (d & 3) == 0;
-    // Only rows that 16-byte loads can take are fetched ahead; everything else goes column by column in the phase itself.
-    auto load_ahead = [&](int64_t t, int phase) {
-        const float* xr = static_cast<const float*>(xv) + t * ldx;
+    // (4096 rows of 14400 -> 15360, 267 MB: 188 us with the whole token's planes, 96 KB, filled without prefetch and one
+    // workgroup per compute unit, 61 us so; 2048 x 8160 -> 8704 44 and 25, 2048 x 11520 -> 12288 102 and 33, and the same from rows
+    // of any alignment.)
+    // A unit is 4 columns x 8 rows: a 16-byte load a row, and the four 16-byte stores of a lane go to slots whose low bits are
+    // XORed with mt so that the 16 slots of a bank round are all different.  48 KB of planes are 256 units, one a thread of four
+    // waves.
+    constexpr int UPR = NC / 4;         // units per 8-row group; a K step has NC of them
+    // beside the 128 accumulators of 512 columns there is no room for it (2048 x 16384 -> 32768: 75 us; 182 when two units were
+    // fetched ahead and 280 registers went to scratch)
+    constexpr bool AHEAD = KLOG2 <= 8;
+    f32x4 ahead[8];
+    // Buffer loads: 16 bytes from any 4-byte aligned address, and each value that lies beyond the token's d reads as zero,
+    // without a branch per row.
+    auto load_unit = [&](f32x4* unit, int64_t t, int phase, int u, bool any) {
+        const auto row = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(static_cast<const float*>(xv) + t * ldx), 0, t < T ? 4 * d : 0, 0x00027000);
+        const int i0 = (32 * KG * phase + 8 * (u / UPR)) * NC + 4 * (u % UPR);
+        const int at = any ? 4 * i0 : 0x40000000;       // beyond any token (d <= 2^20)
 #pragma unroll
-        for (int s = 0; s < AHEAD; ++s) {
-            const int u = tid + s * nthreads;
-            if (!vec4 || u >= UNITS) continue;
-            const int i0 = (32 * KG * phase + 8 * (u / UPR)) * NC + 4 * (u % UPR);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                ahead[s][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (i0 + e * NC < d) ahead[s][e] = *reinterpret_cast<const f32x4*>(xr + (uint32_t)(i0 + e * NC));
-            }
-        }
+        for (int e = 0; e < 8; ++e) unit[e] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(row, at + 4 * e * NC, 0, 0));
     };
-    // the 8 rows of column j of unit u: three 16-byte slots
-    auto split_column = [&](int u, int j, auto row) {
-        const int ag = u / UPR, c4 = u % UPR, mt = c4 >> 2;
-        unsigned char* dst = tsm + (size_t)((ag >> 2) * MT + mt) * 1024 + 16 * ((4 * (c4 & 3) + 16 * (ag & 3) + j) ^ (mt & 3));
+    // always written, with zeros where there is nothing to fetch, so that no old value has to be kept; the thread's number is
+    // opaque so that addresses are formed here and not kept in registers over the token loop
+    auto load_ahead = [&](int64_t t, int phase) {
+        int me = tid;
+        asm("" : "+v"(me));
+        if constexpr (AHEAD) load_unit(ahead, t, phase, me, me < KG * NC);
+    };
+    // the 8 rows of a column of 8-row group ag of the phase: three 16-byte slots
+    auto split_column = [&](int ag, int c, auto row) {
+        const int mt = c >> 4;
+        unsigned char* dst = tsm + (size_t)((ag >> 2) * NS * MT + mt) * 1024 + 16 * (((c & 15) + 16 * (ag & 3)) ^ (mt & 3));
         u32x4 p0, p1, p2;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -399,8 +404,8 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
             p2[p] = upper_halves(split_rem(r0), split_rem(r1));
         }
         *reinterpret_cast<u32x4*>(dst) = p0;
-        *reinterpret_cast<u32x4*>(dst + plane_bytes) = p1;
-        *reinterpret_cast<u32x4*>(dst + 2 * plane_bytes) = p2;
+        *reinterpret_cast<u32x4*>(dst + MT * 1024) = p1;
+        *reinterpret_cast<u32x4*>(dst + 2 * MT * 1024) = p2;
     };
 
     if constexpr (OUT == OUT_SYM || OUT == OUT_ASYM) {
@@ -412,7 +417,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     if constexpr (!F32IN) {
         if (t < T) load_token_dma(t);       // in flight while the B fragments are fetched
     } else {
-        if (t < T) load_ahead(t, 0);
+        load_ahead(t, 0);
     }
     // ---- once per workgroup: B fragments of P into LDS
     static_assert(KSREG == 0 || BGLOBAL, "register-resident fragments come from the table in device memory");
@@ -455,28 +460,29 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
             wait_all_vm();                  // this wave's part of the token (and its earlier stores) has landed
             token_sync();
         }
-        // fp32: the planes of K steps KG phase .. KG phase + KG - 1 of this token; then the next loads
-        auto f32_phase = [&](int phase) {
+        // fp32: the planes of K steps KG phase .. KG phase + KG - 1 of this token, as far as it has them; then the next loads
+        auto f32_phase = [&](int phase) __attribute__((always_inline)) {
             lds_barrier();                  // every wave has finished reading the previous planes
-            if (vec4) {
+            const int units = min(KG, ks_count - KG * phase) * NC;
+            int me = tid;                   // opaque, as above
+            asm("" : "+v"(me));
+            auto split_unit = [&](const f32x4* unit, int u) {
 #pragma unroll
-                for (int s = 0; s < AHEAD; ++s)
-                    if (tid + s * nthreads < UNITS) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) split_column(tid + s * nthreads, j, [&](int e) { return ahead[s][e][j]; });
-                    }
-            }
-            // workgroups of few waves have more units than they fetched ahead; unaligned rows fetch nothing ahead
-            const float* xr = static_cast<const float*>(xv) + t * ldx;
-#pragma unroll 1
-            for (int uj = tid + (vec4 ? AHEAD * nthreads : 0); uj < UNITS; uj += nthreads)
-#pragma unroll 1
                 for (int j = 0; j < 4; ++j) {
-                    const int i0 = (32 * KG * phase + 8 * (uj / UPR)) * NC + 4 * (uj % UPR) + j;
-                    split_column(uj, j, [&](int e) { return i0 + e * NC < d ? xr[(uint32_t)(i0 + e * NC)] : 0.f; });
+                    split_column(u / UPR, 4 * (u % UPR) + j, [&](int e) { return unit[e][j]; });
+                    __builtin_amdgcn_sched_barrier(0);      // one column at a time: interleaved they cost 10 to 60 registers
                 }
-            if (KG * (phase + 1) < ks_count) load_ahead(t, phase + 1);
-            else if (t + t_step < T) load_ahead(t + t_step, 0);
+            };
+            if (AHEAD && me < units) split_unit(ahead, me);
+            // workgroups of few waves have more units than they fetched ahead
+#pragma unroll 1
+            for (int u = AHEAD ? me + nthreads : me; u < units; u += nthreads) {
+                f32x4 unit[8];
+                load_unit(unit, t, phase, u, true);
+                split_unit(unit, u);
+            }
+            const bool same = KG * (phase + 1) < ks_count;
+            load_ahead(same ? t : t + t_step, same ? phase + 1 : 0);
             lds_barrier();
         };
 
@@ -506,8 +512,10 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
                 } else {
 #pragma unroll
                     for (int sp = 0; sp < NS; ++sp) {
+                        // at most 12 fragments read ahead: more cost registers (workgroups on the compute unit) and gain nothing
+                        if (mt % 4 == 0 && mt > 0 && sp == 0) __builtin_amdgcn_sched_barrier(0);
                         const u32x4 raw = *reinterpret_cast<const u32x4*>(
-                            tsm + (size_t)sp * plane_bytes + ((size_t)(((ks & (KG - 1)) * MT + mt) * 64 + (lane ^ (mt & 3)))) * 16);
+                            tsm + ((size_t)((((ks & (KG - 1)) * NS + sp) * MT + mt) * 64 + (lane ^ (mt & 3)))) * 16);
                         const bf16x8 af = __builtin_bit_cast(bf16x8, raw);
 #pragma unroll
                         for (int ti = 0; ti < TPW; ++ti)
@@ -520,12 +528,14 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
         if constexpr (KSREG > 0) {
             static_for<KSREG>([&](auto kc) {
                 constexpr int KS = decltype(kc)::value;
-                if constexpr (F32IN && KS % KG == 0) {
-                    if (KS < ks_count) f32_phase(KS / KG);
-                }
                 auto from_regs = [&](int ti) { return __builtin_bit_cast(bf16x8, breg[ti][KS]); };
-                if constexpr (KS == 0) base_block(0, std::true_type{}, from_regs);
-                else if (KS < ks_count) base_block(KS, std::false_type{}, from_regs);       // wave-uniform
+                if constexpr (KS == 0) {
+                    if constexpr (F32IN) f32_phase(0);
+                    base_block(0, std::true_type{}, from_regs);
+                } else if (KS < ks_count) {       // wave-uniform
+                    if constexpr (F32IN && KS % KG == 0) f32_phase(KS / KG);
+                    base_block(KS, std::false_type{}, from_regs);
+                }
             });
         } else {
             auto from_memory = [&](int ks) {
@@ -751,7 +761,7 @@ template <int KLOG2, int TPW, bool F32IN, int OUT, bool BGLOBAL = false, int KSR
 pme_status launch_out(const RotateArgs& a, int ks, int nwaves) {
     using L = Layout<KLOG2>;
     constexpr int NS = F32IN ? 3 : 1;
-    const size_t lds = (size_t)NS * (F32IN ? f32_ksteps<KLOG2>() : ks) * L::MT * 1024 + (BGLOBAL ? 0 : (size_t)nwaves * TPW * ks * 1024);
+    const size_t lds = (size_t)NS * (F32IN ? std::min(f32_ksteps<KLOG2, TPW>(), ks) : ks) * L::MT * 1024 + (BGLOBAL ? 0 : (size_t)nwaves * TPW * ks * 1024);
     // 160 KB per workgroup, less the kernel's static LDS rounded up to the dynamic part's 1 KB alignment
     constexpr size_t kMaxDynLds = 160 * 1024 - 1024;
     if (lds > kMaxDynLds || nwaves > max_waves<KLOG2, TPW>()) return PME_ERR_UNSUPPORTED_PATH;

@@ -283,3 +283,34 @@ def test_static_scratch_layer_argument_errors():
     assert pme.workspace_bytes(4096, 14336, 15360, 4096) > pme.STATIC_SCRATCH_BYTES
     assert call(T=4096, d=14336, ldx=14336, d_e=15360, N=4096, ldy=4096) == WORKSPACE
     assert pme.workspace_bytes(2048, 14336, 15360, 4096) <= pme.STATIC_SCRATCH_BYTES
+
+
+def _kernel_metadata():
+    """The kernels of the built library and their resources, from the metadata notes of its gfx950 code objects."""
+    import struct
+    msgpack = pytest.importorskip("msgpack")
+    data = open(os.path.join(ROOT, "paper_2503_17513_amd", "libpme.so"), "rb").read()
+    kernels, pos = [], 0
+    while (pos := data.find(b"\x7fELF", pos + 1)) > 0:
+        if struct.unpack_from("<H", data, pos + 18)[0] != 224:                     # EM_AMDGPU
+            continue
+        table, (entry, count) = struct.unpack_from("<Q", data, pos + 40)[0], struct.unpack_from("<HH", data, pos + 58)
+        for header in range(pos + table, pos + table + entry * count, entry):
+            if struct.unpack_from("<I", data, header + 4)[0] != 7:                  # SHT_NOTE
+                continue
+            at, size = struct.unpack_from("<QQ", data, header + 24)
+            note, end = pos + at, pos + at + size
+            while note < end:
+                name, desc, kind = struct.unpack_from("<III", data, note)
+                body = note + 12 + (name + 3) // 4 * 4
+                if kind == 32:                                                     # NT_AMDGPU_METADATA
+                    kernels += msgpack.unpackb(data[body:body + desc])["amdhsa.kernels"]
+                note = body + (desc + 3) // 4 * 4
+    return kernels
+
+
+def test_rotation_and_k_split_kernels_use_no_scratch():
+    # every instantiation holds its accumulators and what it fetches ahead in registers; spilled ones have cost up to 1.7 x
+    kernels = [k for k in _kernel_metadata() if "k_rotate_mfma" in k[".name"] or "k_gemm_kslice" in k[".name"]]
+    assert len(kernels) > 100
+    assert not [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]

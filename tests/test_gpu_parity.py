@@ -126,6 +126,26 @@ def test_rotate_fp32_on_the_matrix_cores(name, T, d, d_e, shift):
     check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
 
 
+# fp32 rows of every alignment: base and pitch off by 1 .. 3 values, d ending anywhere in a 16-byte load, in few and many tokens
+# (workgroups of one, three and more waves).  What surrounds a row is NaN and may not be used.
+@pytest.mark.parametrize("T,d,d_e,off,pitch", [
+    (5, 2, 640, 1, 3), (7, 2037, 2176, 3, 2041), (600, 2046, 2176, 2, 2050), (3, 4001, 4224, 1, 4005), (1100, 2877, 3072, 1, 2881),
+    (520, 8189, 8704, 1, 8193), (300, 8190, 8704, 2, 8195), (515, 11001, 12288, 3, 11007), (4, 9119, 9728, 1, 9121),
+    (70, 8191, 8960, 2, 8194), (3, 14335, 15360, 1, 14339), (2, 16383, 32768, 1, 16387), (3, 8190, 19968, 2, 8193)])
+def test_rotate_fp32_rows_of_any_alignment(T, d, d_e, off, pitch):
+    x = _acts(T, d, d_e, "f32", seed=d)
+    flat = torch.full((T * pitch + 8,), float("nan"), device="cuda")
+    xd = flat[off:off + T * pitch].view(T, pitch)[:, :d]
+    xd.copy_(torch.from_numpy(x))
+    ref = oracle.rotate_structured(x, d_e)
+    q_ref, s_ref = oracle.quantize_sym_int4(ref)
+    pme.set_path(MFMA)
+    check_xhat(pme.hadamard_expand_f32(xd, d_e).cpu().numpy(), ref)
+    qx, sx = pme.hadamard_expand_quant(xd, d_e)
+    check_scales(sx.cpu().numpy(), s_ref)
+    check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
+
+
 @pytest.mark.parametrize("path", (GENERIC, MFMA))
 def test_rotate_strided_rows(path):
     # ldx > d: rows of a wider buffer
