@@ -897,6 +897,9 @@ pme_status launch_rotate_mfma(const RotateArgs& in) {
         const int nw = (nt + tpw - 1) / tpw, most = (tpw == 1 && a.k <= 8) || a.k == 6 ? kMaxWaves : kMaxWaves / 2;
         a.plain_if_cold = nw > most || (3 * (nc / 16) + nw * tpw) * ks > 159;      // KB
     }
+    // fp32, 257 .. 511 tokens of five tiles: two workgroups of five waves share a compute unit only with fewer registers than this
+    // kernel has; three-wave ones do (511 x 8704: 11.0 us, 13.4 with one tile per wave)
+    if (f32 && a.k == 7 && nt == 5 && a.T > 256 && a.T < 512) tpw = 2;
     if (g_tpw_override > 0) tpw = g_tpw_override;
     // P fragments read from the table in device memory instead of LDS:
     //  * 2^k = 64 with 8 tiles or more (orders 132 .. 152: 8448, 8960, 9728): staging nt ks KB of fragments
@@ -908,7 +911,8 @@ pme_status launch_rotate_mfma(const RotateArgs& in) {
     // them in registers for all its tokens: another 3-6 % (8448 .. 9728, 8704, 15360).
 #define PME_ROTG(K, TP, KS, NWAVES) (f32 ? launch_one<K, TP, true, true, KS>(a, ks, NWAVES) : launch_one<K, TP, false, true, KS>(a, ks, NWAVES))
     if (g_tpw_override == 0) {
-        if (a.k == 6 && nt >= 8) {
+        // (fp32, few tokens and more than four K steps: one tile per wave, 9728 from 9120 values, 8 tokens 7.5 us, 9.2 with two)
+        if (a.k == 6 && nt >= 8 && !(f32 && a.T < 512 && ks > 4 && nt <= kMaxWaves)) {
             // from about 3000 tokens three tiles per wave (three waves per token, five tokens in flight per compute
             // unit) beat two (8448 .. 9728: 5-11 % at 4096 and 8192 tokens; 1-4 % slower at 2048)
             if (!f32 && nt <= 16 && ks <= 4 && a.T >= 3072) return launch_one<6, 3, false, true, 4>(a, ks, (nt + 2) / 3);
