@@ -65,16 +65,28 @@ template <int KLOG2> struct Layout {
     static constexpr int reg_of_run_pos(int j) { return kRegOfRun.v[j]; }
 };
 
+// lane bit 4 (5) <-> the register bit that distinguishes r0 / r1
+__device__ __forceinline__ void swap16(uint32_t& r0, uint32_t& r1) {
+    const u32x2 v = __builtin_amdgcn_permlane16_swap(r0, r1, false, false);
+    r0 = v.x;
+    r1 = v.y;
+}
+__device__ __forceinline__ void swap32(uint32_t& r0, uint32_t& r1) {
+    const u32x2 v = __builtin_amdgcn_permlane32_swap(r0, r1, false, false);
+    r0 = v.x;
+    r1 = v.y;
+}
 __device__ __forceinline__ void swap16(float& r0, float& r1) {
-    // lane bit 4 <-> the register bit that distinguishes r0 / r1
-    u32x2 v = __builtin_amdgcn_permlane16_swap(__float_as_uint(r0), __float_as_uint(r1), false, false);
-    r0 = __uint_as_float(v.x);
-    r1 = __uint_as_float(v.y);
+    uint32_t a = __float_as_uint(r0), b = __float_as_uint(r1);
+    swap16(a, b);
+    r0 = __uint_as_float(a);
+    r1 = __uint_as_float(b);
 }
 __device__ __forceinline__ void swap32(float& r0, float& r1) {
-    u32x2 v = __builtin_amdgcn_permlane32_swap(__float_as_uint(r0), __float_as_uint(r1), false, false);
-    r0 = __uint_as_float(v.x);
-    r1 = __uint_as_float(v.y);
+    uint32_t a = __float_as_uint(r0), b = __float_as_uint(r1);
+    swap32(a, b);
+    r0 = __uint_as_float(a);
+    r1 = __uint_as_float(b);
 }
 
 template <int NREG, int BIT> __device__ __forceinline__ void butterfly(float (&v)[NREG]) {
@@ -131,32 +143,31 @@ template <int KLOG2> __device__ __forceinline__ int run_start(int l4, int l5) {
     return L::RUN * (l4 + 2 * l5);
 }
 
-// Reductions over the 16 lanes of a row and over the wavefront, result in every lane: data-parallel moves within the
-// row (xor 1, xor 2, mirrored halves, mirrored row), then the two row swaps.  A chain of vector instructions; the same
-// steps through ds_bpermute cost an LDS round trip each, twelve in a row for the asymmetric range, which no other work
-// of the wave covers.
-template <class Op> __device__ __forceinline__ float row_reduce(float v, Op op) {
-    auto step = [&](auto ctrl) {
-        const int moved = __builtin_amdgcn_mov_dpp((int)__float_as_uint(v), decltype(ctrl)::value, 0xF, 0xF, true);
-        v = op(v, __uint_as_float((uint32_t)moved));
-    };
+// Maxima over the 16 lanes of a row and over the wavefront, result in every lane, of values that are not negative: their bit
+// patterns compare like unsigned integers, whose maximum takes the data-parallel move (xor 1, xor 2, mirrored halves, mirrored
+// row) as an operand and needs no canonical form -- one instruction a step where the float maximum takes three.  The same steps
+// through ds_bpermute cost an LDS round trip each, which no other work of the wave covers.
+__device__ __forceinline__ uint32_t row_max(uint32_t v) {
+    auto step = [&](auto ctrl) { v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, decltype(ctrl)::value, 0xF, 0xF, true)); };
     step(std::integral_constant<int, 0xB1>{});     // quad_perm [1, 0, 3, 2]
     step(std::integral_constant<int, 0x4E>{});     // quad_perm [2, 3, 0, 1]
     step(std::integral_constant<int, 0x141>{});    // row_half_mirror
     step(std::integral_constant<int, 0x140>{});    // row_mirror
     return v;
 }
-template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op op) {
-    v = row_reduce(v, op);
-    float a = v, b = v;
-    swap16(a, b);
-    a = op(a, b);
-    b = a;
-    swap32(a, b);
-    return op(a, b);
+// The maximum over both rows of each half of the wavefront.
+__device__ __forceinline__ uint32_t half_max(uint32_t v) {
+    v = row_max(v);
+    uint32_t w = v;
+    swap16(v, w);
+    return max(v, w);
 }
-struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fmaxf(a, b); } };
-struct OpMin { __device__ __forceinline__ float operator()(float a, float b) const { return __builtin_fminf(a, b); } };
+// Lower half of the wavefront: the maximum of a over the half's own lanes and their partners in the other; upper half: of b.
+__device__ __forceinline__ uint32_t pair_max(uint32_t a, uint32_t b) {
+    swap32(a, b);
+    return max(a, b);
+}
+__device__ __forceinline__ uint32_t magnitude(float f) { return __float_as_uint(f) & 0x7FFFFFFFu; }
 
 // Exact remainder of f after its truncation to bf16 (the upper half of its bits).
 __device__ __forceinline__ float split_rem(float f) { return f - __uint_as_float(__float_as_uint(f) & 0xFFFF0000u); }
@@ -308,7 +319,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
     const int plane_bytes = (F32IN ? min(KG, ks_count) : ks_count) * MT * 1024;     // one bf16 copy of the K-padded token (fp32: of KG K steps)
 
     extern __shared__ __align__(1024) unsigned char smem[];   // NS token planes, then the B fragments
-    __shared__ float red[2 * kRedSlots];
+    __shared__ uint32_t red[2 * kRedSlots];
     static_assert(kMaxWaves <= kRedSlots, "a row of 16 lanes reduces the waves' ranges");
 
     static_assert(!(MULTI && F32IN), "the multi-token variant takes bf16 input");
@@ -410,7 +421,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
 
     if constexpr (OUT == OUT_SYM || OUT == OUT_ASYM) {
         // the slots of waves that do not exist; the first barrier of the token loop separates this from their readers
-        if (threadIdx.x < 2 * kRedSlots && (int)(threadIdx.x % kRedSlots) >= nwaves) red[threadIdx.x] = 0.f;
+        if (threadIdx.x < 2 * kRedSlots && (int)(threadIdx.x % kRedSlots) >= nwaves) red[threadIdx.x] = 0;
     }
     const int64_t t_step = MULTI ? (int64_t)gridDim.x * nwaves_hw : gridDim.x;
     int64_t t = MULTI ? (int64_t)blockIdx.x * nwaves_hw + wave_hw : blockIdx.x;
@@ -649,23 +660,29 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
                     hi = __builtin_fmaxf(__builtin_fmaxf(hi, v[ti][i]), v[ti][i + 1]);
                     lo = __builtin_fminf(__builtin_fminf(lo, v[ti][i]), v[ti][i + 1]);
                 }
-            lo = wave_reduce(lo, OpMin{});
         } else {
 #pragma unroll
             for (int ti = 0; ti < TPW; ++ti)
 #pragma unroll
                 for (int i = 0; i < NREG; i += 2) hi = __builtin_fmaxf(__builtin_fmaxf(hi, __builtin_fabsf(v[ti][i])), __builtin_fabsf(v[ti][i + 1]));
         }
-        hi = wave_reduce(hi, OpMax{});
+        // one chain for both ends of the range: after the first exchange the lower half of the wavefront reduces the upper end
+        // and the upper half the magnitude of the lower end (symmetric codes: both the same)
+        uint32_t ends = half_max(pair_max(magnitude(hi), magnitude(OUT == OUT_ASYM ? lo : hi)));
         if (nwaves > 1) {
             // the scratch is reused per token: the barrier of the matrix phase separates the tokens
-            if (lane == 0) { red[wave] = hi; red[kRedSlots + wave] = lo; }
+            if ((lane & 31) == 0) red[(lane >> 5) * kRedSlots + wave] = ends;
             lds_barrier();
             // lane l of a row takes wave l's value (0, which changes neither range, beyond the last wave): one read and
             // four steps in place of one dependent read per wave
-            hi = row_reduce(red[l15], OpMax{});
-            if constexpr (OUT == OUT_ASYM) lo = row_reduce(red[kRedSlots + l15], OpMin{});
+            ends = row_max(red[(lane >> 5) * kRedSlots + l15]);
         }
+        if constexpr (OUT == OUT_ASYM) {
+            uint32_t lower = ends;
+            swap32(ends, lower);            // the lower half's value in every lane, and the upper half's
+            lo = -__uint_as_float(lower);
+        }
+        hi = __uint_as_float(ends);
 
         float s = 1.f, rinv = 0.f;
         int z = 0;

@@ -126,6 +126,27 @@ def test_rotate_fp32_on_the_matrix_cores(name, T, d, d_e, shift):
     check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
 
 
+# Ranges with one end at zero, and no range: the first input alone makes every rotated value the same (row 0 of the Hadamard
+# matrix is all ones).  One wave per token, several tokens per workgroup, and up to ten waves, whose ranges meet in LDS.
+@pytest.mark.parametrize("T,d_e", [(5, 640), (1100, 640), (1500, 3072), (6, 8448), (3100, 9728), (600, 10240), (6, 15360), (4, 19968), (3, 32768)])
+@pytest.mark.parametrize("in_dtype", ("bf16", "f32"))
+def test_one_sided_and_empty_ranges(T, d_e, in_dtype):
+    d = min(d_e * 3 // 4 // 8 * 8, 8192)
+    first = np.resize(np.array([1.5, -2.0, 0.0, -0.0, 3.0], np.float32), T)
+    x = torch.zeros((T, d), device="cuda")
+    x[:, 0] = torch.from_numpy(first).cuda()
+    x = x.to(torch.bfloat16) if in_dtype == "bf16" else x
+    pme.set_path(MFMA)
+    qx, sx, zx = (t.cpu().numpy() for t in pme.hadamard_expand_quant_asym(x, d_e))
+    size = np.abs(first) / np.float64(d_e) ** 0.5
+    check_scales(sx, np.where(first == 0, 1.0, size / 15).astype(np.float32))
+    assert np.array_equal(zx, np.where(first < 0, 15, 0))
+    assert (qx == np.where(first > 0, 0xFF, 0)[:, None]).all()
+    qx, sx = (t.cpu().numpy() for t in pme.hadamard_expand_quant(x, d_e))
+    check_scales(sx, np.where(first == 0, 1.0, size / 7).astype(np.float32))
+    assert (qx == np.where(first > 0, 0x77, np.where(first < 0, 0x99, 0))[:, None]).all()
+
+
 # fp32 rows of every alignment: base and pitch off by 1 .. 3 values, d ending anywhere in a 16-byte load, in few and many tokens
 # (workgroups of one, three and more waves).  What surrounds a row is NaN and may not be used.
 @pytest.mark.parametrize("T,d,d_e,off,pitch", [
