@@ -241,7 +241,7 @@ GEMM_CASES = [
     ("decode_one_token_long_k", 1, 520, 15360, (GENERIC, MFMA)),
     ("decode_five_tokens_odd_chunks_ragged_n", 5, 36, 640, (GENERIC, MFMA)),
     ("decode_nine_tokens", 9, 50, 640, (GENERIC, MFMA)),
-    # 17 .. 64 tokens: the weight-streaming kernel with 2, 3 or 4 groups of 16 tokens
+    # 17 .. 64 tokens: the weight-streaming kernel with 2, 3 or 4 groups of 16 tokens, and the shape that takes a K-split tile
     ("decode_17_tokens", 17, 64, 256, (GENERIC, MFMA)),
     ("decode_33_tokens_odd_chunks_ragged_n", 33, 100, 640, (GENERIC, MFMA)),
     ("decode_48_tokens", 48, 40, 384, (GENERIC, MFMA)),
@@ -305,10 +305,14 @@ def test_gemm_every_tile_configuration(tile, d_e):
 # The K-split kernel, every tile (ids 29 .. 34): T and N at a tile edge, one past it and one short of it; the shortest K
 # (a step for every wave), K whose steps do not divide by the waves, and an output pitch that 16-byte stores cannot take.
 # Exact integers: any missing, doubled or misplaced partial sum shows.
-@pytest.mark.parametrize("d_e", (1024, 1152, 2176, 3840))
+K_SPLIT_TILES = ((32, 32), (64, 32), (64, 64), (96, 64), (128, 64), (128, 128))
+
+
+@pytest.mark.parametrize("d_e", (1024, 1152, 2176, 3840, 9856))
 @pytest.mark.parametrize("tile", range(29, 35))
 def test_gemm_k_split_tiles(tile, d_e):
-    bm, bn = ((32, 32), (64, 32), (64, 64), (96, 64), (128, 64), (128, 128))[tile - 29]
+    bm, bn = K_SPLIT_TILES[tile - 29]
+    pme.set_path(MFMA)              # a tile that refused would otherwise be answered by the plain kernel
     rng = np.random.default_rng(tile + d_e)
     for T, N in ((70, bn), (2 * bm + 1, 2 * bn - 1), (max(65, bm), 3 * bn + 8), (65, 5)):
         qx = rng.integers(-8, 8, (T, d_e)).astype(np.int8)
@@ -319,6 +323,7 @@ def test_gemm_k_split_tiles(tile, d_e):
         qxd, qwd = pme.pack_int4(torch.from_numpy(qx)), pme.pack_int4(torch.from_numpy(qw))
         sxd, swd = torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
         pme.set_gemm_tile(tile)
+        assert pme.gemm_plan(T, d_e, N).startswith(f"k_gemm_kslice<{bm}, {bn}, ")
         assert np.array_equal(pme.w4a4_gemm_i32(qxd, qwd).cpu().numpy(), acc)
         y = torch.full((T, N + 3), 9.0, dtype=torch.bfloat16, device="cuda")
         pme.w4a4_gemm(qxd, sxd, qwd, swd, y[:, :N])
@@ -330,6 +335,35 @@ def test_gemm_k_split_tiles(tile, d_e):
         ref = acc + (8 - zx.astype(np.int64))[:, None] * qw.astype(np.int64).sum(1)[None, :]
         check_bf16(ya.float().cpu().numpy(), oracle.dequant_bf16(ref, sx, sw))
         pme.set_gemm_tile(0)
+
+
+@pytest.mark.parametrize("tile", range(29, 35))
+def test_gemm_k_split_extreme_sums(tile):
+    # the largest x256 accumulators that the matrix-core kernels admit: (-8) (-8) at every step of the longest K
+    T, N, d_e = 70, 40, (1 << 17) - 128
+    qx = torch.full((T, d_e // 2), 0x88, dtype=torch.uint8, device="cuda")
+    qw = torch.full((N, d_e // 2), 0x88, dtype=torch.uint8, device="cuda")
+    pme.set_path(MFMA)
+    pme.set_gemm_tile(tile)
+    assert pme.gemm_plan(T, d_e, N).startswith("k_gemm_kslice<%d, %d, " % K_SPLIT_TILES[tile - 29])
+    assert bool((pme.w4a4_gemm_i32(qx, qw) == 64 * d_e).all())
+
+
+# The automatic choice on either side of its lines: few tokens, small outputs, one round of 128 x 128.
+@pytest.mark.parametrize("T,d_e,N,kernel", [
+    (2, 12288, 2112, "k_gemm_decode"), (1, 12288, 4160, "k_gemm_kslice<32, 32,"), (20, 8704, 1000, "k_gemm_kslice<32, 32,"),
+    (58, 1024, 5056, "k_gemm_decode"), (48, 8704, 6144, "k_gemm_kslice<64, 32,"), (70, 1024, 9000, "k_gemm_mfma<64, 64,"),
+    (333, 9728, 1999, "k_gemm_kslice<64, 64,"), (517, 8704, 2048, "k_gemm_kslice<96, 64,"), (700, 8704, 4096, "k_gemm_kslice<128, 128,"),
+    (700, 4352, 4000, "k_gemm_mfma<128, 128,")])
+def test_gemm_automatic_choice(T, d_e, N, kernel):
+    g = torch.Generator(device="cuda").manual_seed(T)
+    qx = torch.randint(0, 256, (T, d_e // 2), dtype=torch.uint8, device="cuda", generator=g)
+    qw = torch.randint(0, 256, (N, d_e // 2), dtype=torch.uint8, device="cuda", generator=g)
+    assert pme.gemm_plan(T, d_e, N).startswith(kernel)
+    pme.set_path(MFMA)
+    acc = pme.w4a4_gemm_i32(qx, qw)
+    rows = torch.unique(torch.cat([torch.arange(0, T, max(1, T // 24)), torch.tensor([T - 1])]))
+    assert np.array_equal(acc[rows.cuda()].cpu().numpy(), oracle.int_gemm(unpack_gpu(qx[rows.cuda()]), unpack_gpu(qw)))
 
 
 @pytest.mark.parametrize("tm,tn", [(8, 1), (1, 8), (4, 2), (2, 4), (16, 16), (3, 5), (24, 8)])
@@ -403,7 +437,7 @@ def test_gemm_asymmetric(path, T):
 
 LAYER_CASES = [("C1", None), ("mid_b68_k5", (300, 2048, 2176, 520)), ("mid_b132_k6", (8, 8192, 8448, 2048)),
                ("mid_b60_k8", (130, 14336, 15360, 260)),
-               # decode: at most 16 tokens through the fused call (weight-streaming GEMM)
+               # decode: at most 16 tokens through the fused call (weight-streaming GEMM; the first one a K-split tile)
                ("decode_b68_k7", (16, 8192, 8704, 530)), ("decode_b60_k8_one_token", (1, 14336, 15360, 300)),
                ("decode_b132_k5", (5, 4096, 4224, 200)), ("decode_folded_b20_k9", (3, 8192, 10240, 100)),
                ("decode_folded_b12_k10", (4, 8192, 12288, 64)), ("decode_b152_k6_ragged_d", (9, 8000, 9728, 1000))]
