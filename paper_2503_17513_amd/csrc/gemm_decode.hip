@@ -1,5 +1,5 @@
-// W4A4 GEMM for decode shapes (at most 64 tokens, in groups of 16): memory-bound on the packed weights.  More than a
-// handful of tokens come here only where d_e is outside the range of the K-split kernel (gemm_kslice.hip).
+// W4A4 GEMM for decode shapes (at most 64 tokens, in groups of 16): memory-bound on the packed weights.  Where a tile of
+// the K-split kernel is estimated faster (gemm_kslice.hip), that takes them.
 //
 //   acc[t][n] = sum_j qx[t][j] qw[n][j],  y[t][n] = bf16(acc * sx[t] * sw[n])   (paper Sections 3 and 4).
 //

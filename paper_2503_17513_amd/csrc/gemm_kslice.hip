@@ -1,14 +1,14 @@
-// W4A4 GEMM for outputs that give a compute unit one small tile: the four waves of a workgroup split K.
+// W4A4 GEMM for outputs that give a compute unit one small tile: the NW = 4 or 8 waves of a workgroup split K.
 //
 //   acc[t][n] = sum_j qx[t][j] qw[n][j],  y[t][n] = bf16(acc * sx[t] * sw[n])   (paper Sections 3 and 4).
 //
-// A workgroup owns a 32 FM x 32 FN output tile.  Wave w takes the K steps w, w + 4, w + 8, ... (128 codes each) and
+// A workgroup owns a 32 FM x 32 FN output tile.  Wave w takes the K steps w, w + NW, w + 2 NW, ... (128 codes each) and
 // computes the whole tile over them, from an LDS ring of its own that it fills by DMA itself: there is no barrier in
 // the K loop, and against waves that share the tile's quarters each fragment read and unpacked feeds twice the matrix
 // instructions.  What bounds the tiled kernel at these sizes is that one wave per SIMD meets a workgroup barrier every
 // 256 codes with little matrix work in between; here a wave only ever waits for its own DMA.  The partial tiles
-// (exact integers) are added through LDS at the end, four 32 x 32 blocks at a time, one per wave, and each wave
-// finishes the block that it added.
+// (exact integers) are added through LDS at the end, four 32 x 32 blocks at a time, one per wave (of eight waves, half of
+// one), and each wave finishes what it added.
 // Operands, unpacking (a nibble in the top of a byte is 16 x its value), fragment layout and epilogue as in gemm_mfma.hip.
 #include "gemm_tile.h"
 

@@ -621,7 +621,8 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
             id = k >= 0 ? 29 + k : wide ? 27 : 24;
         }
     }
-    // ids 29 .. 34: the waves of a workgroup split K
+    // ids 29 .. 34: the waves of a workgroup split K.  Of the tiles below the choice above takes 2, 8, 9, 11, 16, 21, 22, 24, 25,
+    // 27 and 28; the others are there for pme_set_gemm_tile only, to be measured against.
     if (id > 28 && id <= 28 + kKsliceTiles) return launch_gemm_kslice(a, id - 29);
     switch (id) {
         case 1: return launch_tile<256, 256, 2, 4, 64, 3>(a);      // 8 waves of 128 x 64
