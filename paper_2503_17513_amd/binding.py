@@ -86,9 +86,15 @@ def _check(status: int, what: str):
         raise PmeError(status, what)
 
 
+# The handle of a device's current stream without building a Stream object (2 of a call's 12 us on the host).  Not part of
+# torch's public interface: a build without it takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the handle of the current device's current stream, without building a Stream object (2 of a call's 12 us on the host)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dtype_code(x: torch.Tensor) -> int:

@@ -855,6 +855,16 @@ def test_fp32_shapes_that_a_cold_capture_refuses(T, d, d_e):
     assert float(marker[0]) == 1.0
 
 
+def test_calls_go_to_the_current_stream(monkeypatch):
+    from paper_2503_17513_amd import binding
+    for side in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(side):
+            assert binding._stream() == side.cuda_stream
+            monkeypatch.setattr(binding, "_raw_stream", None)
+            assert binding._stream() == side.cuda_stream
+            monkeypatch.undo()
+
+
 def test_probe_mfma():
     # every accumulator grows by the same amount per instruction: the checksum is linear in iters
     out = torch.zeros(512 * 256, dtype=torch.int32, device="cuda")
