@@ -7,7 +7,7 @@
 // one ds_read_b128 brings) and one E8M0 byte per lane for each operand, so nothing is unpacked: packed
 // codes and scale bytes travel HBM -> LDS by DMA (same staged ring as the int4 kernel) and LDS -> MFMA.
 // Accumulation is fp32 in the matrix core; the epilogue rounds to bf16 and stores 16-byte row pieces.
-#include "pme_internal.h"
+#include "gemm_tile.h"
 
 #include <algorithm>
 #include <cstdio>
@@ -20,30 +20,10 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-#define PME_AS3 __attribute__((address_space(3)))
-
-template <int RB> __device__ __forceinline__ int swz(int r) {
-    return RB == 64 ? (((r >> 2) ^ r) & 3) : (r & 7);
-}
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// DMA of 16 / 4 bytes per lane into LDS at lds_base + 16 / 4 * lane (lds_base wave-uniform).  Overwrites M0,
-// which the compiler does not keep values in; nothing else in this kernel makes the compiler use M0.
-// The source is a wave-uniform 64-bit base (SGPR pair) plus a 32-bit byte offset per lane.
-__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
-}
+// As dma16, 4 bytes per lane.
 __device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
-}
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    const bf16x2 p = __builtin_convertvector(f32x2{a, b}, bf16x2);
-    return __builtin_bit_cast(uint32_t, p);
 }
 
 // BM x BN output tile, WGM x WGN waves, RB packed bytes (2 RB codes, RB / 16 scale bytes) per row and K step.

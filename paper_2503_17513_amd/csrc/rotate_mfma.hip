@@ -19,7 +19,7 @@
 // Waves split the token by a' (16-wide tiles, TPW tiles per wave); the FWHT never crosses a'.
 // Since S_{2^k} = S_{2^f} (x) S_{2^(k-f)}, the launcher may hand the kernel the same H as a larger block
 // P_b (x) S_{2^f} times fewer columns (see launch_rotate_mfma): steps 2 and 3 are unaware of it.
-#include "pme_internal.h"
+#include "dma.h"
 
 #include <algorithm>
 #include <mutex>
@@ -271,18 +271,6 @@ template <int MT> __device__ __forceinline__ int chunk_of(int a, int c) {
     return ((a >> 2) * MT + (c >> 4)) * 8 + (a & 3) * 2 + ((c >> 3) & 1);
 }
 
-// LDS-only barrier and DMA helpers.  The DMA and the waits on it are inline assembly so that the
-// compiler does not order LDS reads of the B fragments or of the reduction scratch after them.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-__device__ __forceinline__ void wait_all_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// 16 bytes per lane from global memory into LDS at lds_base + 16 * lane (lds_base wave-uniform); lanes
-// switched off by the caller's branch move nothing.  Overwrites M0, which the compiler does not keep
-// values in; no other code in this kernel makes the compiler emit an M0 use.
-__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_base) {
-    // wave-uniform 64-bit base in SGPRs plus a 32-bit byte offset per lane
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
-}
-
 // One workgroup handles tokens blockIdx.x, blockIdx.x + gridDim.x, ...  The token buffer in LDS is
 // refilled for the next token as soon as the matrix-core phase of the current one has consumed it,
 // so the HBM read of token i + 1 runs under the FWHT / quantize / store phase of token i.
@@ -468,7 +456,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
 
     for (; t < T; t += t_step) {
         if constexpr (!F32IN) {
-            wait_all_vm();                  // this wave's part of the token (and its earlier stores) has landed
+            wait_vm<0>();                  // this wave's part of the token (and its earlier stores) has landed
             token_sync();
         }
         // fp32: the planes of K steps KG phase .. KG phase + KG - 1 of this token, as far as it has them; then the next loads
@@ -755,7 +743,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
         }
         }   // int4 outputs
     }
-    wait_all_vm();
+    wait_vm<0>();
 }
 
 // Workgroups of `threads` threads and `lds` bytes of dynamic LDS that one compute unit holds at once, as the runtime
