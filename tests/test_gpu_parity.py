@@ -126,6 +126,18 @@ def test_rotate_fp32_on_the_matrix_cores(name, T, d, d_e, shift):
     check_codes(unpack_gpu(qx), q_ref, ref, s_ref)
 
 
+@pytest.mark.parametrize("d", (16384, 20000, 30000))
+def test_rotate_fp32_512_columns_is_as_exact_as_the_plain_kernel(d):
+    # 32768 from fp32 went to the matrix cores, which add three terms of every input: their sum must not be rounded more often
+    # than the plain kernel's butterflies round (2-norms over 8 x 32768 values vary by a few per mille; measured ratio 0.93)
+    x = _acts(8, d, 32768, "f32", seed=d)
+    ref, xd, err = oracle.rotate_structured(x, 32768), to_device(x, "f32"), []
+    for path in (MFMA, GENERIC):
+        pme.set_path(path)
+        err.append(np.linalg.norm(pme.hadamard_expand_f32(xd, 32768).cpu().numpy().astype(np.float64) - ref))
+    assert err[0] <= err[1]
+
+
 # Ranges with one end at zero, and no range: the first input alone makes every rotated value the same (row 0 of the Hadamard
 # matrix is all ones).  One wave per token, several tokens per workgroup, and up to ten waves, whose ranges meet in LDS.
 @pytest.mark.parametrize("T,d_e", [(5, 640), (1100, 640), (1500, 3072), (6, 8448), (3100, 9728), (600, 10240), (6, 15360), (4, 19968), (3, 32768)])
