@@ -171,6 +171,9 @@ __device__ __forceinline__ uint32_t magnitude(float f) { return __float_as_uint(
 
 // Exact remainder of f after its truncation to bf16 (the upper half of its bits).
 __device__ __forceinline__ float split_rem(float f) { return f - __uint_as_float(__float_as_uint(f) & 0xFFFF0000u); }
+// The same of an input.  The maximum leaves every remainder of a finite value alone and makes the NaN that an infinite one
+// leaves finite, so that the sum of the three terms is infinite as the input is (1 % of the fp32 rotation).
+__device__ __forceinline__ float split_rem_input(float f) { return __builtin_fmaxf(split_rem(f), -3.0e38f); }
 // The upper halves of two fp32 values in one dword, f0's in the low half.
 __device__ __forceinline__ uint32_t upper_halves(float f0, float f1) {
     return __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
@@ -397,7 +400,7 @@ k_rotate_mfma(const void* __restrict__ xv, int64_t ldx, int T, int d, int d_e, i
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             const float f0 = row(2 * p), f1 = row(2 * p + 1);
-            const float r0 = split_rem(f0), r1 = split_rem(f1);
+            const float r0 = split_rem_input(f0), r1 = split_rem_input(f1);
             p0[p] = upper_halves(f0, f1);
             p1[p] = upper_halves(r0, r1);
             p2[p] = upper_halves(split_rem(r0), split_rem(r1));

@@ -138,6 +138,22 @@ def test_rotate_fp32_512_columns_is_as_exact_as_the_plain_kernel(d):
     assert err[0] <= err[1]
 
 
+@pytest.mark.parametrize("path", (GENERIC, MFMA))
+@pytest.mark.parametrize("d,d_e", [(2037, 2176), (8192, 8704), (14336, 15360), (8192, 19968), (30000, 32768)])
+def test_rotate_fp32_infinite_and_nan_inputs(d, d_e, path):
+    # one infinite input makes its whole token infinite (and the token's scale), a NaN makes it NaN; other tokens are untouched
+    x = _acts(4, d, d_e, "f32", seed=d)
+    ref = oracle.rotate_structured(x[3:], d_e)
+    for t, v in enumerate((np.inf, -np.inf, np.nan)):
+        x[t, d - 1 - t] = v
+    pme.set_path(path)
+    xd = to_device(x, "f32")
+    xhat, (_, sx) = pme.hadamard_expand_f32(xd, d_e).cpu().numpy(), pme.hadamard_expand_quant(xd, d_e)
+    assert np.isinf(xhat[:2]).all() and np.isnan(xhat[2]).all()
+    assert np.isinf(sx[:2].cpu().numpy()).all()
+    check_xhat(xhat[3:], ref)
+
+
 # Ranges with one end at zero, and no range: the first input alone makes every rotated value the same (row 0 of the Hadamard
 # matrix is all ones).  One wave per token, several tokens per workgroup, and up to ten waves, whose ranges meet in LDS.
 @pytest.mark.parametrize("T,d_e", [(5, 640), (1100, 640), (1500, 3072), (6, 8448), (3100, 9728), (600, 10240), (6, 15360), (4, 19968), (3, 32768)])
