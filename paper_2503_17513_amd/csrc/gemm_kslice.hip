@@ -394,7 +394,7 @@ double loader64_cost(int64_t T, int64_t N, int64_t d_e) {
 // The K-split tile that is estimated to beat `other` us by more than 4 %, or -1.  Its time over that of the kernel it replaces,
 // on the 3900 fitted outputs of up to 6144 channels: from the caches 0.92 in the mean up to 16 tokens, 0.61 up to 64 and 0.72
 // above, beyond 1.03 on 30 outputs; from memory 0.98, 0.82 and 0.79, beyond 1.03 on one output in ten (mostly 12 .. 32 tokens
-// by less than 2048 channels, 20 % at most, where it gains 30 % from the caches).
+// by less than 2048 channels, up to 1.28, where it gains 30 % from the caches).
 int kslice_choice(int64_t T, int64_t N, int64_t d_e, double other) {
     if (!kslice_range(d_e)) return -1;
     double best = 0.96 * other;
