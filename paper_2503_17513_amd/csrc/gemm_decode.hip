@@ -32,7 +32,9 @@ k_gemm_decode(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ qw,
               const int32_t* __restrict__ zx, const int32_t* __restrict__ wsum,
               int T, int N, int kb, void* __restrict__ out, int64_t ldo) {
     __shared__ int part[NW][64][4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // The wave's number is read into a scalar register, so that the conditions on its share of K are branches: a matrix
+    // instruction takes no notice of the execution mask, and one that is only masked runs on registers nothing was loaded into.
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, kg = lane >> 4;
     const int n0 = blockIdx.x * 16;
     const int nchunks = kb >> 6;

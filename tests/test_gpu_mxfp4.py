@@ -88,6 +88,26 @@ def test_mxfp4_gemm(name, T, N, d_e, paths):
         check_mx_gemm(y, qx, ex, qw, ew)
 
 
+@pytest.mark.parametrize("T", (17, 32))
+@pytest.mark.parametrize("d_e", (256, 384, 512, 640, 896, 1152))
+def test_mxfp4_gemm_two_groups_of_tokens_on_few_chunks(T, d_e):
+    """17 .. 32 tokens where some of a workgroup's waves have one 128-code chunk and others none or two: a wave without a
+    second chunk must not run its matrix instruction (outputs were NaN now and then, from registers never written)."""
+    rng = np.random.default_rng(d_e + T)
+    N = 592
+    qx = rng.integers(0, 16, size=(T, d_e), dtype=np.uint8)
+    qw = rng.integers(0, 16, size=(N, d_e), dtype=np.uint8)
+    ex = rng.integers(118, 132, size=(T, d_e // 32), dtype=np.uint8)
+    ew = rng.integers(118, 130, size=(N, d_e // 32), dtype=np.uint8)
+    args = [torch.from_numpy(a).cuda() for a in (oracle.pack_fp4(qx), ex, oracle.pack_fp4(qw), ew)]
+    pme.set_path(MFMA)
+    x = torch.randn((64, 512), device="cuda")
+    for _ in range(5):
+        pme.hadamard_expand_quant(x, 512)          # leaves values of another kernel in the registers
+        y = pme.mxfp4_gemm(*args).to(torch.float32).cpu().numpy()
+        check_mx_gemm(y, qx, ex, qw, ew)
+
+
 @pytest.mark.parametrize("tile", range(1, 12))
 def test_mxfp4_gemm_every_tile(tile):
     rng = np.random.default_rng(tile)
