@@ -21,14 +21,23 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// As dma16, 4 bytes per lane.
-__device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_base) : "memory");
+// As dma16, from a buffer: bytes beyond its end arrive as zeros.
+__device__ __forceinline__ void dma16_buffer(u32x4 rsrc, uint32_t voff, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff), "s"(rsrc), "s"(lds_base) : "memory");
+}
+// Buffer descriptor of `bytes` bytes at p.
+__device__ __forceinline__ u32x4 buffer_of(const void* p, uint32_t bytes) {
+    const uint64_t a = (uint64_t)(uintptr_t)p;
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00027000u};
 }
 
 // BM x BN output tile, WGM x WGN waves, RB packed bytes (2 RB codes, RB / 16 scale bytes) per row and K step.
 // LOADER: one more wave per workgroup issues every DMA (codes and scale bytes of every stage) and waits for them;
 // the matrix waves issue none (as in the int4 kernel: issuing a DMA holds a wave up for tens of cycles).
+// Scale bytes travel in groups of 512 codes, sixteen bytes a row, through a ring of two groups of their own: a DMA that takes a
+// few bytes from each of 64 rows touches 64 lines where one of codes touches 8 or 16, and costs as much or more, so the four
+// bytes of every 128 codes cost as much again as the codes (GEMM alone, us, then and now: 4096 x 4096 x 15360 on 256 x 256 of four
+// waves 163 and 139, on 128 x 128 218 and 187; 2048 x 2048 x 8704 on 128 x 128 30.8 and 28.7).
 template <int BM, int BN, int WGM, int WGN, int RB, int NSTAGE, bool LOADER = false>
 __global__ void __launch_bounds__(64 * (WGM * WGN + (LOADER ? 1 : 0)))
 k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, const uint8_t* __restrict__ qw,
@@ -40,10 +49,11 @@ k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, co
     constexpr int CPR = RB / 16, RPB = 64 / CPR, BLKS = ROWS / RPB;
     constexpr int CH = (BLKS + NW - 1) / NW;          // code DMA instructions per wave per stage
     constexpr int SW = RB / 64;                       // scale dwords per row per K step
-    constexpr int SBLKS = (ROWS / 64) * SW;           // scale DMA blocks (64 rows x 4 bytes) per stage
-    constexpr int SCH = (SBLKS + NW - 1) / NW;        // scale DMA instructions per wave per stage
-    constexpr int CODE_BYTES = ROWS * RB;
-    constexpr int STAGE = CODE_BYTES + ROWS * 4 * SW;
+    constexpr int GS = 4 / SW;                        // K steps per group of scales (512 codes)
+    constexpr int SBLKS = ROWS / 64;                  // scale DMA blocks (64 rows x 16 bytes) per group
+    constexpr int SCH = (SBLKS + NW - 1) / NW;        // scale DMA instructions per wave per group
+    constexpr int STAGE = ROWS * RB, SCALES = NSTAGE * STAGE, GROUP = ROWS * 16;
+    static_assert(GS >= NSTAGE - 1, "a group of scales lands before its first reader (see the K loop)");
     constexpr int NSUB = RB / 32;                     // MFMA K steps (64 codes) per K step
     constexpr int SLAB = 32 * WN * 2;
     static_assert(ROWS % 64 == 0, "scale DMA moves 64 rows at a time");
@@ -59,14 +69,23 @@ k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, co
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(PME_AS3 unsigned char*)smem;
     const int KT = kb / RB;
+    // group g of the scales: bytes 16 g .. 16 g + 15 of a row (beyond the row's end those of the next row, which nobody uses)
+    const u32x4 ex_buf = buffer_of(ex, (uint32_t)T * (uint32_t)eb), ew_buf = buffer_of(ew, (uint32_t)N * (uint32_t)eb);
+    auto scale_row = [&](int blk) {                   // byte offset of this lane's row of scale block blk
+        const int r = 64 * blk + lane;
+        return (uint32_t)((r < BM) ? min(m0 + r, T - 1) : min(n0 + r - BM, N - 1)) * (uint32_t)eb;
+    };
+    auto issue_scale_block = [&](int g, int blk, uint32_t row_off) {
+        dma16_buffer(64 * blk < BM ? ex_buf : ew_buf, row_off + 16 * g,
+                     __builtin_amdgcn_readfirstlane(lds0 + SCALES + (g & 1) * GROUP + blk * 1024));
+    };
     if constexpr (LOADER) {
         if (wave == NW) {
             // The loader wave meets the matrix waves at their barriers (one before the K loop, one per K step, one
             // after the loop) and leaves after the last; later barriers count the waves still running.
             static_assert(RPB % (RB == 64 ? 16 : 8) == 0, "the swizzle must not depend on the block");
-            constexpr int PER_STAGE = BLKS + SBLKS;
-            constexpr int FIRST_WAIT = (NSTAGE - 1) * PER_STAGE < 63 ? (NSTAGE - 1) * PER_STAGE : 63;   // vmcnt has 6 bits
-            static_assert((NSTAGE - 2) * PER_STAGE <= 63, "the wait count of the K loop must fit vmcnt");
+            constexpr int FIRST_WAIT = (NSTAGE - 1) * BLKS < 63 ? (NSTAGE - 1) * BLKS : 63;   // vmcnt has 6 bits
+            static_assert((NSTAGE - 2) * BLKS <= 63, "the wait count of the K loop must fit vmcnt");
             const int lr = lane / CPR, kc = (lane % CPR) ^ swz<RB>(lr);
             uint32_t off[BLKS], soff[SBLKS];
 #pragma unroll
@@ -76,32 +95,30 @@ k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, co
                 off[blk] = (uint32_t)row * (uint32_t)kb + (uint32_t)(kc * 16);
             }
 #pragma unroll
-            for (int sb = 0; sb < SBLKS; ++sb) {
-                const int plane = sb / (ROWS / 64), r = 64 * (sb % (ROWS / 64)) + lane;
-                const int row = (r < BM) ? min(m0 + r, T - 1) : min(n0 + r - BM, N - 1);
-                soff[sb] = (uint32_t)row * (uint32_t)eb + (uint32_t)(4 * plane);
-            }
+            for (int sb = 0; sb < SBLKS; ++sb) soff[sb] = scale_row(sb);
             auto issue_stage = [&](int stage, int kt) {
                 const uint8_t* pa = qx + (int64_t)kt * RB;
                 const uint8_t* pb = qw + (int64_t)kt * RB;
-                const uint8_t* sa = ex + (int64_t)kt * (RB / 16);
-                const uint8_t* sb_ = ew + (int64_t)kt * (RB / 16);
 #pragma unroll
                 for (int blk = 0; blk < BLKS; ++blk)
                     dma16(blk < BM / RPB ? pa : pb, off[blk], lds0 + stage * STAGE + blk * 1024);
-#pragma unroll
-                for (int sb = 0; sb < SBLKS; ++sb)
-                    dma4(64 * (sb % (ROWS / 64)) < BM ? sa : sb_, soff[sb], lds0 + stage * STAGE + CODE_BYTES + sb * 256);
             };
+            auto issue_scales = [&](int g) {
+#pragma unroll
+                for (int sb = 0; sb < SBLKS; ++sb) issue_scale_block(g, sb, soff[sb]);
+            };
+            issue_scales(0);
+            issue_scales(1);
 #pragma unroll
             for (int st = 0; st < NSTAGE; ++st) issue_stage(st, min(st, KT - 1));
             wait_vm<FIRST_WAIT>();
             lds_barrier();
             int cur = 0;
             for (int kt = 0; kt + 1 < KT; ++kt) {
-                wait_vm<(NSTAGE - 2) * PER_STAGE>();
+                wait_vm<(NSTAGE - 2) * BLKS>();
                 lds_barrier();          // K step kt + 1 has landed; every wave has left the stage of K step kt
                 issue_stage(cur, min(kt + NSTAGE, KT - 1));
+                if ((kt + 1) % GS == 0) issue_scales((kt + 1) / GS + 1);
                 cur = (cur == NSTAGE - 1) ? 0 : cur + 1;
             }
             wait_vm<0>();
@@ -121,30 +138,17 @@ k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, co
         const int row = (r < BM) ? min(m0 + r, T - 1) : min(n0 + r - BM, N - 1);
         voff[s] = (uint32_t)row * (uint32_t)kb + (uint32_t)(kc * 16);
     }
-    // scale bytes: block sb = plane * (ROWS / 64) + rows-of-64 index; lane = row within the 64
+    // scale blocks beyond the last repeat an earlier one, so that every wave issues the same number
     uint32_t svoff[SCH];
 #pragma unroll
-    for (int s = 0; s < SCH; ++s) {
-        const int sb = (wave + NW * s) % SBLKS;
-        const int plane = sb / (ROWS / 64), r = 64 * (sb % (ROWS / 64)) + lane;
-        const int row = (r < BM) ? min(m0 + r, T - 1) : min(n0 + r - BM, N - 1);
-        svoff[s] = (uint32_t)row * (uint32_t)eb + (uint32_t)(4 * plane);
-    }
-    // DMA slot q of this wave for K step kt: slots 0 .. CH - 1 move codes, CH .. CH + SCH - 1 scale bytes
-    constexpr int NSLOT = CH + SCH;
+    for (int s = 0; s < SCH; ++s) svoff[s] = scale_row((wave + NW * s) % SBLKS);
     auto issue_slot = [&](int stage, int kt, int q) {
-        if (q < CH) {
-            const int blk = (wave + NW * q) % BLKS;
-            dma16((blk < BM / RPB ? qx : qw) + (int64_t)kt * RB, voff[q], lds0 + stage * STAGE + blk * 1024);
-        } else {
-            const int sb = (wave + NW * (q - CH)) % SBLKS;
-            dma4((64 * (sb % (ROWS / 64)) < BM ? ex : ew) + (int64_t)kt * (RB / 16), svoff[q - CH],
-                 lds0 + stage * STAGE + CODE_BYTES + sb * 256);
-        }
+        const int blk = (wave + NW * q) % BLKS;
+        dma16((blk < BM / RPB ? qx : qw) + (int64_t)kt * RB, voff[q], lds0 + stage * STAGE + blk * 1024);
     };
-    auto issue = [&](int stage, int kt) {
+    auto issue_scales = [&](int g) {
 #pragma unroll
-        for (int q = 0; q < NSLOT; ++q) issue_slot(stage, kt, q);
+        for (int s = 0; s < SCH; ++s) issue_scale_block(g, (wave + NW * s) % SBLKS, svoff[s]);
     };
 
     f32x16 acc[FM][FN];
@@ -156,37 +160,29 @@ k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, co
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
     const int frow = lane & 31, fk = lane >> 5;
-    int aoff[FM], boff[FN], asoff[FM], bsoff[FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-        const int r = wm * WM + 32 * i + frow;
-        aoff[i] = r * RB + ((fk ^ swz<RB>(r)) << 4);
-        asoff[i] = CODE_BYTES + r * 4;
-    }
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const int r = BM + wn * WN + 32 * j + frow;
-        boff[j] = r * RB + ((fk ^ swz<RB>(r)) << 4);
-        bsoff[j] = CODE_BYTES + r * 4;
-    }
+    // of the wave's first token and channel fragment within a stage and within a group of scales; the others follow at
+    // constant distances (rows 32 apart share their swizzle)
+    const int aoff = (wm * WM + frow) * RB + ((fk ^ swz<RB>(frow)) << 4), boff = (BM + wn * WN + frow) * RB + ((fk ^ swz<RB>(frow)) << 4);
+    const int asoff = SCALES + (wm * WM + frow) * 16, bsoff = SCALES + (BM + wn * WN + frow) * 16;
     struct Frags { u32x4 a[FM], b[FN]; uint32_t sa[FM], sb[FN]; };
-    // sub-step s: codes of block 2 s + fk of the row (chunk position (2 s + fk) ^ swz), and its scale: byte
-    // (2 s + fk) & 3 of scale dword (2 s + fk) >> 2 = s >> 1.  The dword is read once per pair of sub-steps
+    // sub-step s of K step kt: codes of block 2 s + fk of the row (chunk position (2 s + fk) ^ swz), and its scale: byte
+    // (2 s + fk) & 3 of dword s >> 1 of the K step's SW.  The dword is read once per pair of sub-steps
     // and shifted by 8 fk bits, which puts the scale of the even sub-step in byte 0 and of the odd one in
     // byte 2; the matrix instruction picks the byte (its scale operand select), so the odd sub-step takes
     // the register of the even one (`even`) and reads nothing.
-    auto load_frags = [&](Frags& f, const unsigned char* stage, int s, const Frags& even) {
+    auto load_frags = [&](Frags& f, const unsigned char* stage, int kt, int s, const Frags& even) {
+        const unsigned char* sc = smem + (kt / GS & 1) * GROUP + 4 * (kt % GS * SW + (s >> 1));
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
-            f.a[i] = *reinterpret_cast<const u32x4*>(stage + (aoff[i] ^ (s << 5)));
+            f.a[i] = *reinterpret_cast<const u32x4*>(stage + (aoff ^ (s << 5)) + 32 * i * RB);
             if (s & 1) f.sa[i] = even.sa[i];
-            else f.sa[i] = *reinterpret_cast<const uint32_t*>(stage + asoff[i] + (s >> 1) * ROWS * 4) >> (8 * fk);
+            else f.sa[i] = *reinterpret_cast<const uint32_t*>(sc + asoff + 512 * i) >> (8 * fk);
         }
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-            f.b[j] = *reinterpret_cast<const u32x4*>(stage + (boff[j] ^ (s << 5)));
+            f.b[j] = *reinterpret_cast<const u32x4*>(stage + (boff ^ (s << 5)) + 32 * j * RB);
             if (s & 1) f.sb[j] = even.sb[j];
-            else f.sb[j] = *reinterpret_cast<const uint32_t*>(stage + bsoff[j] + (s >> 1) * ROWS * 4) >> (8 * fk);
+            else f.sb[j] = *reinterpret_cast<const uint32_t*>(sc + bsoff + 512 * j) >> (8 * fk);
         }
     };
     // formats 4 = FP4 E2M1 for both operands; odd: the sub-step's scales sit in byte 2 of the scale registers
@@ -212,58 +208,77 @@ k_mxgemm_mfma(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, co
 
     // Pipeline over sub-steps g = kt NSUB + s: read the fragments of g + 1 while the matrix cores work on g.
     // Before the region whose read first touches K step kt + 1 (s = NSUB - 1) every read of K step kt has been
-    // issued: wait for the DMA of kt + 1, barrier, start the DMA of kt + NSTAGE into the stage just left.
+    // issued: wait for the DMA of kt + 1, barrier; the stage just left is refilled with K step kt + NSTAGE over this region and
+    // the PARTS - 1 that follow, the DMA instructions between the matrix instructions.  A compute unit moves 64 bytes a cycle
+    // into LDS, so all of a refill in one region takes longer than the region's matrix work (4096 x 4096 x 15360 on 256 x 256 of
+    // four waves 138 us in one region, 132 over two, 138 over three, whose last pieces arrive late; with three stages over all
+    // regions: on 256 x 128 167 and 149, 2048 x 2048 x 8704 on 128 x 128 28.7 and 27.1).
+    // The K step before a group of scales begins fetches the next group, into the place of the one it ends: GS steps, and as
+    // many refills, before its first reader's wait, which leaves NSTAGE - 2 refills in flight.
+    constexpr int PARTS = NSTAGE == 2 ? 2 : NSUB;
+    // slots of part p: [slot0(p), slot0(p + 1))
+    auto slot0 = [](int p) { return (CH * p + PARTS - 1) / PARTS; };
     if constexpr (!LOADER) {
+        issue_scales(0);
+        issue_scales(1);
+        // the last stage's later parts follow in the first regions of K step 0
 #pragma unroll
-        for (int st = 0; st < NSTAGE; ++st) issue(st, min(st, KT - 1));
-        wait_vm<(NSTAGE - 1) * (CH + SCH)>();
+        for (int st = 0; st < NSTAGE; ++st)
+#pragma unroll
+            for (int q = 0; q < (st == NSTAGE - 1 ? slot0(1) : CH); ++q) issue_slot(st, min(st, KT - 1), q);
+        wait_vm<(NSTAGE - 2) * CH + slot0(1)>();
     }
     lds_barrier();
+    // the matrix instructions of a sub-step with DMA slots [Q0, Q1) of K step kt between them
+    auto mfma_and_dma = [&](const Frags& f, bool odd, int stage, int kt, auto q0, auto q1) {
+        constexpr int Q0 = decltype(q0)::value, NQ = decltype(q1)::value - Q0, NM = FM * FN;
+        constexpr int NP = NQ == 0 ? 1 : NM < NQ ? NM : NQ;
+        static_for<NP>([&](auto pc) {
+            constexpr int c = decltype(pc)::value;
+            static_for<NM>([&](auto mc) {
+                if constexpr (decltype(mc)::value * NP / NM == c) mfma_one(f, mc, odd);
+            });
+            if constexpr (NQ > 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<NQ>([&](auto qc) {
+                    if constexpr (decltype(qc)::value * NP / NQ == c) issue_slot(stage, kt, Q0 + decltype(qc)::value);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+    };
     Frags raw[2];
-    load_frags(raw[0], smem, 0, raw[0]);
+    load_frags(raw[0], smem, 0, 0, raw[0]);
     int cur = 0;
     for (int kt = 0; kt + 1 < KT; ++kt) {
-        const int nxt = (cur == NSTAGE - 1) ? 0 : cur + 1;
+        const int nxt = (cur == NSTAGE - 1) ? 0 : cur + 1, prv = (cur == 0) ? NSTAGE - 1 : cur - 1;
         const unsigned char* scur = smem + cur * STAGE;
         const unsigned char* snxt = smem + nxt * STAGE;
-#pragma unroll
-        for (int s = 0; s < NSUB; ++s) {
-            if (LOADER && s == NSUB - 1) {
+        static_for<NSUB>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if constexpr (s == NSUB - 1) {
+                if constexpr (!LOADER) wait_vm<(NSTAGE - 2) * CH>();
                 lds_barrier();
-                load_frags(raw[(s + 1) & 1], snxt, 0, raw[s & 1]);
-                mfma_all(raw[s & 1], (s & 1) != 0);
-            } else if (s == NSUB - 1) {
-                wait_vm<(NSTAGE - 2) * (CH + SCH)>();
-                lds_barrier();
-                load_frags(raw[(s + 1) & 1], snxt, 0, raw[s & 1]);
-                // refill the stage just left with K step kt + NSTAGE: the DMA instructions go between the
-                // matrix instructions, which keep the pipe busy while the wave is held up issuing them
-                const int ktn = min(kt + NSTAGE, KT - 1);
-                constexpr int NM = FM * FN;
-                constexpr int NP = NM < NSLOT ? NM : NSLOT;
-                static_for<NP>([&](auto pc) {
-                    constexpr int c = decltype(pc)::value;
-                    static_for<NM>([&](auto mc) {
-                        if constexpr (decltype(mc)::value * NP / NM == c) mfma_one(raw[s & 1], mc, (s & 1) != 0);
-                    });
-                    __builtin_amdgcn_sched_barrier(0);
-                    static_for<NSLOT>([&](auto qc) {
-                        if constexpr (decltype(qc)::value * NP / NSLOT == c) issue_slot(cur, ktn, decltype(qc)::value);
-                    });
-                    __builtin_amdgcn_sched_barrier(0);
-                });
+                if constexpr (!LOADER) {
+                    if ((kt + 1) % GS == 0) issue_scales((kt + 1) / GS + 1);
+                }
+                load_frags(raw[(s + 1) & 1], snxt, kt + 1, 0, raw[s & 1]);
+                if constexpr (LOADER) mfma_all(raw[s & 1], (s & 1) != 0);
+                else mfma_and_dma(raw[s & 1], (s & 1) != 0, cur, min(kt + NSTAGE, KT - 1), std::integral_constant<int, 0>{}, std::integral_constant<int, slot0(1)>{});
             } else {
-                load_frags(raw[(s + 1) & 1], scur, s + 1, raw[s & 1]);
-                mfma_all(raw[s & 1], (s & 1) != 0);
+                load_frags(raw[(s + 1) & 1], scur, kt, s + 1, raw[s & 1]);
+                if constexpr (LOADER || s + 2 > PARTS) mfma_all(raw[s & 1], (s & 1) != 0);
+                else mfma_and_dma(raw[s & 1], (s & 1) != 0, prv, min(kt + NSTAGE - 1, KT - 1), std::integral_constant<int, slot0(s + 1)>{},
+                                  std::integral_constant<int, slot0(s + 2)>{});
             }
-        }
+        });
         cur = nxt;
     }
     {
         const unsigned char* scur = smem + cur * STAGE;
 #pragma unroll
         for (int s = 0; s < NSUB; ++s) {
-            if (s + 1 < NSUB) load_frags(raw[(s + 1) & 1], scur, s + 1, raw[s & 1]);
+            if (s + 1 < NSUB) load_frags(raw[(s + 1) & 1], scur, KT - 1, s + 1, raw[s & 1]);
             mfma_all(raw[s & 1], (s & 1) != 0);
         }
     }
@@ -324,7 +339,7 @@ pme_status launch_tile(const MxGemmArgs& a) {
     }
     const int tiles_m = (int)((a.T + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * (WGM * WGN + (LOADER ? 1 : 0)));
-    const size_t lds = (size_t)NSTAGE * ((BM + BN) * RB + (BM + BN) * 4 * (RB / 64));
+    const size_t lds = (size_t)(BM + BN) * (NSTAGE * RB + 32);
     auto kern = k_mxgemm_mfma<BM, BN, WGM, WGN, RB, NSTAGE, LOADER>;
     static std::atomic<uint32_t> done;
     if (lds > 64 * 1024 && allow_dynamic_lds(kern, (int)lds, done) != PME_OK) return PME_ERR_HIP;
@@ -529,7 +544,7 @@ pme_status launch_mxgemm_mfma(const MxGemmArgs& a) {
             const double c192 = rounds_shared(tiles(128, 192)) * (128.0 * 192.0) / 0.55;
             const double c128 = rounds_shared(tiles(128, 128)) * (128.0 * 128.0) / 0.47;
             const double best = std::min(std::min(c256, c9), std::min(c192, c128));
-            if (best == c256) id = wide ? 8 : 2;
+            if (best == c256) id = wide ? (a.d_e >= 1024 ? 1 : 8) : 2;
             else if (best == c9) id = 9;
             else if (best == c192) id = tiles(128, 192) > cus ? 5 : (wide ? 6 : 10);
             else id = wide ? 3 : 4;

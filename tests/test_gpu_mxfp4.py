@@ -123,6 +123,26 @@ def test_mxfp4_gemm_every_tile(tile):
     check_mx_gemm(y, qx, ex, qw, ew)
 
 
+# Scale bytes arrive in groups of 512 codes: less than one group, whole ones, a remainder of 128 and of 256 codes, and more
+# groups than the two of the ring; the last rows' remainder lies at the end of the scale tensors.
+@pytest.mark.parametrize("d_e", (256, 512, 1152, 1792, 2560))
+@pytest.mark.parametrize("tile", range(1, 12))
+def test_mxfp4_gemm_scale_groups(tile, d_e):
+    if d_e % 256 and tile in (1, 3, 6, 8, 9):      # 128-byte rows
+        pytest.skip("the tile takes whole steps of 256 codes")
+    rng = np.random.default_rng(tile + d_e)
+    T, N = 65, 72
+    qx = rng.integers(0, 16, size=(T, d_e), dtype=np.uint8)
+    qw = rng.integers(0, 16, size=(N, d_e), dtype=np.uint8)
+    ex = rng.integers(112, 136, size=(T, d_e // 32), dtype=np.uint8)
+    ew = rng.integers(112, 136, size=(N, d_e // 32), dtype=np.uint8)
+    args = [torch.from_numpy(a).cuda() for a in (oracle.pack_fp4(qx), ex, oracle.pack_fp4(qw), ew)]
+    pme.set_path(MFMA)
+    pme.set_gemm_tile(100 + tile)
+    y = pme.mxfp4_gemm(*args).to(torch.float32).cpu().numpy()
+    check_mx_gemm(y, qx, ex, qw, ew)
+
+
 @pytest.mark.parametrize("shape", ((40, 2048, 2176, 200), (130, 8192, 8704, 300)))
 def test_mxfp4_layer_end_to_end(shape):
     T, d, d_e, N = shape
