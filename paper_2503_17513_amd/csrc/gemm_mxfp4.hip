@@ -10,6 +10,7 @@
 #include "gemm_tile.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <string>
 #include <type_traits>
@@ -489,7 +490,65 @@ pme_status launch_mx_decode_groups(const MxGemmArgs& a) {
     return launch_mx_decode_nw<4, TG>(a);
 }
 
+// ---- choice of the kernel from d_e = 1024 on, by estimated time.  Fitted (least squares of the relative error) to 10 000
+// outputs of 1 .. 8192 tokens, 64 .. 28672 channels and d_e 1024 .. 32768, each timed with every tile as the layer runs it: after the
+// rotation that writes its codes, three sets of operands in turn.  On a quarter of them, held back, the chosen kernel is within 1 %
+// (1.5 % at 17 .. 64 tokens) of the fastest in the mean.  Layer over that of the earlier choice (streaming up to 16 or 32 tokens,
+// 64 x 64 tiles of a shared K loop, 128 x 128 and more), in the mean: 0.78 up to 16 tokens, 0.58 up to 64, 0.59 up to 256, 0.72 up to
+// 1024, 0.83 up to 4096.
+struct MxCost { int id, bm, bn; bool lines; int least; double c[8]; };      // lines: 128-byte rows; least: smallest d_e
+const MxCost kMxCosts[] = {
+    {1, 256, 256, true, 1024, {13.37, 10.71, 0.673, 0.2116, 0.3177, 0.668, 0, 0.2102}},
+    {2, 256, 256, false, 1024, {12.44, 9.307, 0.6866, 0.2065, 0.3358, 0.7205, 0.001417, 0.2217}},
+    {3, 128, 128, true, 1024, {5.243, 2.511, 0.247, 0.07281, 0.1013, 0.2466, 0, 0.3631}},
+    {4, 128, 128, false, 1024, {4.45, 0.514, 0.3381, 0.1047, 0.2229, 0.1743, 0, 0.3999}},
+    {5, 128, 192, false, 1024, {4.629, 0, 0.4188, 0.1437, 0.282, 0.3135, 0.005861, 0.2597}},
+    {9, 256, 128, true, 1024, {7.819, 4.466, 0.4075, 0.09392, 0.1507, 0.4027, 0, 0.4078}},
+    {11, 64, 64, false, 1024, {2.199, 0, 0.2147, 0.03845, 0.08489, 0.05854, 0, 0.9751}},
+    {12, 128, 64, true, 1024, {3.214, 0, 0.2173, 0.02465, 0.07099, 0.1357, 0, 0.6059}},
+    {13, 192, 128, true, 1024, {6.44, 3.345, 0.3475, 0.07093, 0.1107, 0.3501, 0, 0.4096}},
+    {14, 256, 192, true, 1024, {8.083, 5.476, 0.5662, 0.1667, 0.2161, 0.5571, 0, 0.2436}},
+    {16, 8, 32, true, 2048, {2.741, 2.034, 0.03171, 0.02939, 0.01963, 0.01139, 0.01063, 10.87}},
+    {17, 16, 32, true, 1024, {2.63, 0.7471, 0.03832, 0.03008, 0.004878, 0.03273, 0.005648, 3.936}},
+    {18, 32, 32, true, 1024, {2.701, 0.9101, 0.04108, 0.03867, 0.01118, 0.05254, 0, 5.633}},
+    {19, 64, 32, true, 1024, {3.121, 0.7524, 0.09128, 0.01802, 0.01022, 0.08921, 0, 3.172}},
+    {20, 64, 64, true, 1024, {3.496, 1.519, 0.1194, 0.0533, 0.003603, 0.1213, 0, 1.56}},
+    {21, 32, 32, false, 1024, {2.499, 0, 0.04835, 0.0492, 0.01977, 0.06, 0, 5.326}},
+};
+// us: c0 + c1 further rounds + steps (c2 + c3 first round's fill + c4 further fill + c5 further rounds + c6 channels / 4096)
+// + c7 outputs / 10^6, K in steps of 128 codes, a round one workgroup on each of the 256 compute units
+double mx_cost(const double (&c)[8], int64_t tiles, int64_t T, int64_t d_e, int64_t N) {
+    const double steps = (double)(d_e / 128), fill = (double)tiles / 256.0, more = std::ceil(fill) - 1.0;
+    return c[0] + c[1] * more + steps * (c[2] + c[3] * std::min(fill, 1.0) + c[4] * std::max(fill - 1.0, 0.0) + c[5] * more + c[6] * (double)N / 4096.0) +
+           c[7] * 1e-6 * (double)T * (double)N;
+}
+// The weight-streaming kernel: workgroups of 16 channels, tokens in groups of 16.
+double mx_decode_cost(int64_t T, int64_t d_e, int64_t N) {
+    const double steps = (double)(d_e / 128), fill = (double)((N + 15) / 16) / 256.0, more = std::ceil(fill) - 1.0, groups = (double)T / 16.0;
+    return 1.79 + 0.096 * more + steps * (0.0633 + 0.0086 * std::min(fill, 1.0) + 0.0286 * std::max(fill - 1.0, 0.0) + 0.0531 * more + 0.0397 * groups + 0.013 * groups * fill);
+}
+int mx_choice(int64_t T, int64_t d_e, int64_t N, double* us) {
+    int id = 0;
+    *us = 1e30;
+    for (const MxCost& k : kMxCosts) {
+        if ((k.lines && d_e % 256) || d_e < k.least) continue;
+        const double c = mx_cost(k.c, ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), T, d_e, N);
+        if (c < *us) { *us = c; id = k.id; }
+    }
+    return id;
+}
+
 }  // namespace
+
+bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N) {
+    if (g_mx_tile_override) return false;
+    // the streaming kernel reads every token's codes once per 16 channels: at most 32 tokens, and 16 where there are many channels
+    if (T > 32 || (T > 16 && N >= 8192)) return false;
+    if (d_e < 1024 || d_e % 128) return true;
+    double us;
+    mx_choice(T, d_e, N, &us);
+    return us > 0.96 * mx_decode_cost(T, d_e, N);
+}
 
 void set_mxgemm_tile_override(int id) { g_mx_tile_override = id; }
 
@@ -525,7 +584,10 @@ pme_status launch_mxgemm_mfma(const MxGemmArgs& a) {
     const int64_t cus = 256;
     auto tiles = [&](int bm, int bn) { return ((a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     int id = g_mx_tile_override;
+    double us;
+    if (id == 0 && a.d_e >= 1024) id = mx_choice(a.T, a.d_e, a.N, &us);
     if (id == 0) {
+        // short K: a few K steps, where prologue and epilogue decide
         const bool wide = (a.d_e % 256) == 0;
         if (tiles(128, 128) >= cus / 2) {
             // The cheapest of four tile shapes by rounds x tile area / efficiency, as in the int4 kernel.  With FP4
@@ -544,7 +606,7 @@ pme_status launch_mxgemm_mfma(const MxGemmArgs& a) {
             const double c192 = rounds_shared(tiles(128, 192)) * (128.0 * 192.0) / 0.55;
             const double c128 = rounds_shared(tiles(128, 128)) * (128.0 * 128.0) / 0.47;
             const double best = std::min(std::min(c256, c9), std::min(c192, c128));
-            if (best == c256) id = wide ? (a.d_e >= 1024 ? 1 : 8) : 2;
+            if (best == c256) id = wide ? 8 : 2;
             else if (best == c9) id = 9;
             else if (best == c192) id = tiles(128, 192) > cus ? 5 : (wide ? 6 : 10);
             else id = wide ? 3 : 4;
@@ -552,6 +614,7 @@ pme_status launch_mxgemm_mfma(const MxGemmArgs& a) {
             id = 11;
         }
     }
+    if (id >= 16) return launch_mxgemm_kslice(a, id - 16);      // 16 .. 21: the waves of a workgroup split K
     switch (id) {
         case 1: return launch_tile<256, 256, 2, 2, 128, 2>(a);
         case 2: return launch_tile<256, 256, 2, 2, 64, 3>(a);
@@ -566,6 +629,9 @@ pme_status launch_mxgemm_mfma(const MxGemmArgs& a) {
         // at 128 x 128 one wave cannot issue a stage's 40 DMA instructions in the time of its 16 matrix instructions per wave)
         case 10: return launch_tile<128, 192, 2, 2, 64, 3, true>(a);
         case 11: return launch_tile<64, 64, 2, 2, 64, 3, true>(a);
+        case 12: return launch_tile<128, 64, 2, 2, 128, 3>(a);
+        case 13: return launch_tile<192, 128, 2, 2, 128, 3>(a);
+        case 14: return launch_tile<256, 192, 2, 2, 128, 2>(a);
     }
     return PME_ERR_UNSUPPORTED_PATH;
 }

@@ -132,10 +132,10 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 pme_status run_mxgemm_slice(const pme::MxGemmArgs& a) {
     int path = g_path.load();
     if (path != PME_PATH_GENERIC) {
-        // few tokens: the weight-streaming kernel, unless the output is wide enough to fill the chip with tiles
-        const bool stream_weights = a.T <= 16 || (a.T <= 32 && a.N < 8192);
+        const bool stream_weights = pme::mxgemm_streams(a.T, a.d_e, a.N);
         pme_status s = stream_weights ? pme::launch_mxgemm_decode(a) : pme::launch_mxgemm_mfma(a);
-        if (s == PME_ERR_UNSUPPORTED_PATH && stream_weights) s = pme::launch_mxgemm_mfma(a);
+        // the streaming kernel takes scale bytes of any alignment, the others more tokens
+        if (s == PME_ERR_UNSUPPORTED_PATH) s = stream_weights ? pme::launch_mxgemm_mfma(a) : pme::launch_mxgemm_decode(a);
         if (s != PME_ERR_UNSUPPORTED_PATH || path == PME_PATH_MFMA) return s;
     }
     return pme::launch_mxgemm_generic(a);

@@ -41,6 +41,8 @@ struct MxGemmArgs {
 pme_status launch_mxgemm_generic(const MxGemmArgs& a);
 pme_status launch_mxgemm_mfma(const MxGemmArgs& a);
 pme_status launch_mxgemm_decode(const MxGemmArgs& a);
+pme_status launch_mxgemm_kslice(const MxGemmArgs& a, int tile);       // 0 .. 5: 8 x 32, 16 x 32, 32 x 32, 64 x 32, 64 x 64, 32 x 32 with 64-byte rows
+bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N);               // the weight-streaming kernel is estimated fastest
 
 struct GemmArgs {
     const uint8_t* qx;

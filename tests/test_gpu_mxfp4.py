@@ -126,9 +126,9 @@ def test_mxfp4_gemm_every_tile(tile):
 # Scale bytes arrive in groups of 512 codes: less than one group, whole ones, a remainder of 128 and of 256 codes, and more
 # groups than the two of the ring; the last rows' remainder lies at the end of the scale tensors.
 @pytest.mark.parametrize("d_e", (256, 512, 1152, 1792, 2560))
-@pytest.mark.parametrize("tile", range(1, 12))
+@pytest.mark.parametrize("tile", range(1, 15))
 def test_mxfp4_gemm_scale_groups(tile, d_e):
-    if d_e % 256 and tile in (1, 3, 6, 8, 9):      # 128-byte rows
+    if d_e % 256 and tile in (1, 3, 6, 8, 9, 12, 13, 14):      # 128-byte rows
         pytest.skip("the tile takes whole steps of 256 codes")
     rng = np.random.default_rng(tile + d_e)
     T, N = 65, 72
@@ -141,6 +141,50 @@ def test_mxfp4_gemm_scale_groups(tile, d_e):
     pme.set_gemm_tile(100 + tile)
     y = pme.mxfp4_gemm(*args).to(torch.float32).cpu().numpy()
     check_mx_gemm(y, qx, ex, qw, ew)
+
+
+# The tiles whose waves split K (16 .. 21: tokens, channels, waves, bytes a row): one token, the tile's edges and beyond, ragged
+# channels (16-byte and single stores); K of one step a wave, shares that differ by one step, a last group of scales cut short.
+KSPLIT = {16: (8, 32, 8, 128), 17: (16, 32, 4, 128), 18: (32, 32, 4, 128), 19: (64, 32, 4, 128), 20: (64, 64, 4, 128), 21: (32, 32, 4, 64)}
+
+
+@pytest.mark.parametrize("tile,d_e", [(t, 2 * k[3] * s) for t, k in KSPLIT.items() for s in (k[2], k[2] + 1, 3 * k[2] - 1, 5 * k[2] + 2)])
+def test_mxfp4_gemm_k_split_tiles(tile, d_e):
+    bm, bn = KSPLIT[tile][:2]
+    rng = np.random.default_rng(tile + d_e)
+    pme.set_path(MFMA)
+    pme.set_gemm_tile(100 + tile)
+    for T, N in ((1, 8), (bm, bn), (bm + 1, bn + 8), (2 * bm - 1, 2 * bn + 3)):
+        qx = rng.integers(0, 16, size=(T, d_e), dtype=np.uint8)
+        qw = rng.integers(0, 16, size=(N, d_e), dtype=np.uint8)
+        ex = rng.integers(112, 136, size=(T, d_e // 32), dtype=np.uint8)
+        ew = rng.integers(112, 136, size=(N, d_e // 32), dtype=np.uint8)
+        args = [torch.from_numpy(a).cuda() for a in (oracle.pack_fp4(qx), ex, oracle.pack_fp4(qw), ew)]
+        guard = torch.full((T + 1, N + 5), 7.0, dtype=torch.bfloat16, device="cuda")
+        pme.mxfp4_gemm(*args, y=guard[:T, :N])
+        y = guard.to(torch.float32).cpu().numpy()
+        check_mx_gemm(y[:T, :N], qx, ex, qw, ew)
+        assert (y[T:] == 7.0).all() and (y[:, N:] == 7.0).all()
+
+
+@pytest.mark.parametrize("T", (5, 20))
+def test_mxfp4_gemm_few_tokens_with_unaligned_scales(T):
+    """Scale rows that are not 4-byte aligned: the streaming kernel takes them, whatever kernel is estimated fastest."""
+    rng = np.random.default_rng(T)
+    N, d_e = 640, 8448
+    qx = rng.integers(0, 16, size=(T, d_e), dtype=np.uint8)
+    qw = rng.integers(0, 16, size=(N, d_e), dtype=np.uint8)
+    ex = rng.integers(112, 136, size=(T, d_e // 32), dtype=np.uint8)
+    ew = rng.integers(112, 136, size=(N, d_e // 32), dtype=np.uint8)
+
+    def odd(a):
+        buf = torch.empty(a.size + 1, dtype=torch.uint8, device="cuda")
+        buf[1:] = torch.from_numpy(a).cuda().flatten()
+        return buf[1:].view(a.shape)
+
+    pme.set_path(MFMA)
+    y = pme.mxfp4_gemm(torch.from_numpy(oracle.pack_fp4(qx)).cuda(), odd(ex), torch.from_numpy(oracle.pack_fp4(qw)).cuda(), odd(ew))
+    check_mx_gemm(y.to(torch.float32).cpu().numpy(), qx, ex, qw, ew)
 
 
 @pytest.mark.parametrize("shape", ((40, 2048, 2176, 200), (130, 8192, 8704, 300)))
