@@ -37,11 +37,19 @@ constexpr int mx_kslice_lds(int ar, int bn, int nw, int rb, int nstage) {
     return rings > parts ? rings : parts;
 }
 
-template <int AR, int BN, int NW, int RB, int NSTAGE>
-__global__ void __launch_bounds__(64 * NW)
-k_mxgemm_kslice(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, const uint8_t* __restrict__ qw,
-                const uint8_t* __restrict__ ew, int T, int N, int kb, int eb, uint16_t* __restrict__ y, int64_t ldo,
-                int tiles_m, int tiles_n, int xcd_gm, int vec_store) {
+struct MxSliceArgs {
+    const uint8_t *qx, *ex, *qw, *ew;
+    int T, N, kb, eb;
+    uint16_t* y;
+    int64_t ldo;
+    int tiles_m, tiles_n, xcd_gm, vec_store;
+};
+
+template <int AR, int BN, int NW, int RB, int NSTAGE> __device__ __forceinline__ void mx_kslice_tile(const MxSliceArgs& args) {
+    const uint8_t *__restrict__ qx = args.qx, *__restrict__ ex = args.ex, *__restrict__ qw = args.qw, *__restrict__ ew = args.ew;
+    uint16_t* __restrict__ y = args.y;
+    const int T = args.T, N = args.N, kb = args.kb, eb = args.eb, tiles_m = args.tiles_m, tiles_n = args.tiles_n, xcd_gm = args.xcd_gm, vec_store = args.vec_store;
+    const int64_t ldo = args.ldo;
     constexpr int BM = (AR + 31) / 32 * 32, FM = BM / 32, FN = BN / 32, ROWS = AR + BN;
     static_assert((AR == 8 || AR == 16 || AR % 32 == 0) && BN % 32 == 0, "whole 32-row fragments, or one that repeats 8 or 16 rows");
     constexpr int CPR = RB / 16, RPB = 64 / CPR;  // 16-byte chunks per row and K step; rows per DMA instruction
@@ -267,10 +275,19 @@ k_mxgemm_kslice(const uint8_t* __restrict__ qx, const uint8_t* __restrict__ ex, 
     });
 }
 
+template <int AR, int BN, int NW, int RB, int NSTAGE> __global__ void __launch_bounds__(64 * NW) k_mxgemm_kslice(MxSliceArgs a) {
+    mx_kslice_tile<AR, BN, NW, RB, NSTAGE>(a);
+}
+// the tiles of few tokens go by the name of the decode kernels
+template <int AR, int BN, int NW, int RB, int NSTAGE> __global__ void __launch_bounds__(64 * NW) k_mxgemm_decode(MxSliceArgs a) {
+    mx_kslice_tile<AR, BN, NW, RB, NSTAGE>(a);
+}
+
 template <int AR, int BN, int NW, int RB, int NSTAGE> pme_status launch_mx_kslice(const MxGemmArgs& a) {
     const int kb = (int)(a.d_e / 2), eb = (int)(a.d_e / 32);
     if (kb % RB || kb < RB * NW) return PME_ERR_UNSUPPORTED_PATH;      // whole K steps, at least one for each wave
     if ((int64_t)std::max(a.T, a.N) * kb >= (int64_t(1) << 32)) return PME_ERR_UNSUPPORTED_PATH;   // 32-bit DMA offsets
+    constexpr bool FEW = AR < 32;
     if (a.dry) {
         if (a.plan) {
             static const std::string name = [] {
@@ -278,19 +295,23 @@ template <int AR, int BN, int NW, int RB, int NSTAGE> pme_status launch_mx_kslic
                 snprintf(buf, sizeof buf, "k_mxgemm_kslice<%d, %d, %d, %d, %d>", AR, BN, NW, RB, NSTAGE);
                 return std::string(buf);
             }();
-            *a.plan = name.c_str();
+            *a.plan = FEW ? "k_mxgemm_decode" : name.c_str();
         }
         return PME_OK;
     }
     const int tiles_m = (int)((a.T + AR - 1) / AR), tiles_n = (int)((a.N + BN - 1) / BN);
     constexpr int lds = mx_kslice_lds(AR, BN, NW, RB, NSTAGE);
     static_assert(lds <= 160 * 1024, "the rings fit in LDS");
-    auto kern = k_mxgemm_kslice<AR, BN, NW, RB, NSTAGE>;
+    constexpr auto kern = [] {
+        if constexpr (FEW) return k_mxgemm_decode<AR, BN, NW, RB, NSTAGE>;
+        else return k_mxgemm_kslice<AR, BN, NW, RB, NSTAGE>;
+    }();
     static std::atomic<uint32_t> done;
     if (lds > 64 * 1024 && allow_dynamic_lds(kern, lds, done) != PME_OK) return PME_ERR_HIP;
     const int vec = (a.N % 8 == 0 && a.ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0) ? 1 : 0;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), lds, a.stream, a.qx, a.ex, a.qw, a.ew, (int)a.T, (int)a.N,
-                       kb, eb, static_cast<uint16_t*>(a.y), a.ldy, tiles_m, tiles_n, xcd_grid_m(tiles_m, tiles_n, AR, BN), vec);
+    const MxSliceArgs args{a.qx, a.ex, a.qw, a.ew, (int)a.T, (int)a.N, kb, eb, static_cast<uint16_t*>(a.y), a.ldy,
+                           tiles_m, tiles_n, xcd_grid_m(tiles_m, tiles_n, AR, BN), vec};
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * NW), lds, a.stream, args);
     return hip_status(hipGetLastError());
 }
 
