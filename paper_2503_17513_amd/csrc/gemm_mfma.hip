@@ -567,6 +567,7 @@ int g_tile_override = 0;
 }  // namespace
 
 void set_gemm_tile_override(int id) { g_tile_override = id; }
+int tile_override() { return g_tile_override; }
 
 pme_status launch_gemm_mfma(const GemmArgs& a) {
     // d_e a multiple of 128 (whole K steps), 16-byte aligned rows, and the x256 accumulator in range:
@@ -617,11 +618,12 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
         } else {
             // Smaller outputs: a K-split tile, or 64 x 64 with a loader wave (short K, many tiles: 700 x 3072 x 2176 takes
             // 10.6 us on it and 13.8 on the best K-split tile), with whole 128-byte lines per K step where d_e allows.
-            const int k = kslice_choice(a.T, a.N, a.d_e, loader64_cost(a.T, a.N, a.d_e));
+            const double other = loader64_cost(a.T, a.N, a.d_e);
+            const int k = a.ksplit >= 0 && a.ksplit_us < 0.96 * other ? a.ksplit : a.ksplit >= 0 ? -1 : kslice_choice(a.T, a.N, a.d_e, other);
             id = k >= 0 ? 29 + k : wide ? 27 : 24;
         }
     }
-    // ids 29 .. 34: the waves of a workgroup split K.  Of the tiles below the choice above takes 2, 8, 9, 11, 16, 21, 22, 24, 25,
+    // ids 29 .. 36: the waves of a workgroup split K.  Of the tiles below the choice above takes 2, 8, 9, 11, 16, 21, 22, 24, 25,
     // 27 and 28; the others are there for pme_set_gemm_tile only, to be measured against.
     if (id > 28 && id <= 28 + kKsliceTiles) return launch_gemm_kslice(a, id - 29);
     switch (id) {

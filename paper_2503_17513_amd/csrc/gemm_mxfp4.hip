@@ -515,13 +515,6 @@ const MxCost kMxCosts[] = {
     {20, 64, 64, true, 1024, {3.496, 1.519, 0.1194, 0.0533, 0.003603, 0.1213, 0, 1.56}},
     {21, 32, 32, false, 1024, {2.499, 0, 0.04835, 0.0492, 0.01977, 0.06, 0, 5.326}},
 };
-// us: c0 + c1 further rounds + steps (c2 + c3 first round's fill + c4 further fill + c5 further rounds + c6 channels / 4096)
-// + c7 outputs / 10^6, K in steps of 128 codes, a round one workgroup on each of the 256 compute units
-double mx_cost(const double (&c)[8], int64_t tiles, int64_t T, int64_t d_e, int64_t N) {
-    const double steps = (double)(d_e / 128), fill = (double)tiles / 256.0, more = std::ceil(fill) - 1.0;
-    return c[0] + c[1] * more + steps * (c[2] + c[3] * std::min(fill, 1.0) + c[4] * std::max(fill - 1.0, 0.0) + c[5] * more + c[6] * (double)N / 4096.0) +
-           c[7] * 1e-6 * (double)T * (double)N;
-}
 // The weight-streaming kernel: workgroups of 16 channels, tokens in groups of 16.
 double mx_decode_cost(int64_t T, int64_t d_e, int64_t N) {
     const double steps = (double)(d_e / 128), fill = (double)((N + 15) / 16) / 256.0, more = std::ceil(fill) - 1.0, groups = (double)T / 16.0;
@@ -532,7 +525,7 @@ int mx_choice(int64_t T, int64_t d_e, int64_t N, double* us) {
     *us = 1e30;
     for (const MxCost& k : kMxCosts) {
         if ((k.lines && d_e % 256) || d_e < k.least) continue;
-        const double c = mx_cost(k.c, ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), T, d_e, N);
+        const double c = tile_cost(k.c, ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn), T, N, d_e);
         if (c < *us) { *us = c; id = k.id; }
     }
     return id;
@@ -540,13 +533,14 @@ int mx_choice(int64_t T, int64_t d_e, int64_t N, double* us) {
 
 }  // namespace
 
-bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N) {
+bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N, int* tile) {
+    *tile = 0;
     if (g_mx_tile_override) return false;
     // the streaming kernel reads every token's codes once per 16 channels: at most 32 tokens, and 16 where there are many channels
     if (T > 32 || (T > 16 && N >= 8192)) return false;
     if (d_e < 1024 || d_e % 128) return true;
     double us;
-    mx_choice(T, d_e, N, &us);
+    *tile = mx_choice(T, d_e, N, &us);
     return us > 0.96 * mx_decode_cost(T, d_e, N);
 }
 
@@ -585,6 +579,7 @@ pme_status launch_mxgemm_mfma(const MxGemmArgs& a) {
     auto tiles = [&](int bm, int bn) { return ((a.T + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     int id = g_mx_tile_override;
     double us;
+    if (id == 0) id = a.tile;
     if (id == 0 && a.d_e >= 1024) id = mx_choice(a.T, a.d_e, a.N, &us);
     if (id == 0) {
         // short K: a few K steps, where prologue and epilogue decide

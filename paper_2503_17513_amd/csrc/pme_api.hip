@@ -88,15 +88,18 @@ pme_status check_gemm(const uint8_t* qx, const uint8_t* qw, int64_t T, int64_t d
 // largest tile edge so that a slice starts on a tile (and vector-store) boundary.
 int64_t max_slice_rows(int64_t row_bytes) { return std::max<int64_t>(256, (((int64_t(1) << 32) - 1) / row_bytes) & ~int64_t(255)); }
 
-pme_status run_gemm_slice(const pme::GemmArgs& a) {
+pme_status run_gemm_slice(pme::GemmArgs a) {
     int path = g_path.load();
     if (path != PME_PATH_GENERIC) {
         // few tokens: the weight-streaming kernel while the output has fewer than 128 tiles of 64 x 64, unless a K-split tile
         // is estimated faster: from two rounds of 4096 channels on and with more tokens, whose codes the streaming kernel
-        // reads once per 16 channels (us from the caches / from memory, streaming and K-split: 1 x 4096 x 12288 8.2 / 8.0 and
-        // 9.8 / 11.9, 1 x 5120 x 12288 13.3 / 13.0 and 9.8 / 12.3, 32 x 4096 x 15360 18.8 / 19.2 and 13.6 / 18.2)
-        const bool stream_weights = (a.T <= 16 || (a.T <= 64 && a.N < 8192)) &&
-                                    pme::kslice_choice(a.T, a.N, a.d_e, pme::decode_cost(a.T, a.N, a.d_e)) < 0;
+        // reads once per 16 channels (layers, us: 8 x 2048 x 8448 10.1 and 9.3, 8 x 1088 x 22016 18.6 and 15.3, 32 x 4096 x 15360
+        // 20 and 15.0)
+        bool stream_weights = !pme::tile_override() && (a.T <= 16 || (a.T <= 64 && a.N < 8192));
+        if (stream_weights) {
+            a.ksplit = pme::kslice_choice(a.T, a.N, a.d_e, pme::decode_cost(a.T, a.N, a.d_e), &a.ksplit_us);
+            stream_weights = a.ksplit < 0;
+        }
         pme_status s = stream_weights ? pme::launch_gemm_decode(a) : pme::launch_gemm_mfma(a);
         if (s == PME_ERR_UNSUPPORTED_PATH && stream_weights && a.T > 16) s = pme::launch_gemm_mfma(a);
         if (s != PME_ERR_UNSUPPORTED_PATH || path == PME_PATH_MFMA) return s;
@@ -129,10 +132,10 @@ pme_status run_gemm(const pme::GemmArgs& a) {
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-pme_status run_mxgemm_slice(const pme::MxGemmArgs& a) {
+pme_status run_mxgemm_slice(pme::MxGemmArgs a) {
     int path = g_path.load();
     if (path != PME_PATH_GENERIC) {
-        const bool stream_weights = pme::mxgemm_streams(a.T, a.d_e, a.N);
+        const bool stream_weights = pme::mxgemm_streams(a.T, a.d_e, a.N, &a.tile);
         pme_status s = stream_weights ? pme::launch_mxgemm_decode(a) : pme::launch_mxgemm_mfma(a);
         // the streaming kernel takes scale bytes of any alignment, the others more tokens
         if (s == PME_ERR_UNSUPPORTED_PATH) s = stream_weights ? pme::launch_mxgemm_mfma(a) : pme::launch_mxgemm_decode(a);
@@ -161,17 +164,19 @@ pme_status run_mxgemm(const pme::MxGemmArgs& a) {
     return PME_OK;
 }
 
-// Rotate + quantize, then the GEMM on the codes.  Both stages are asked first whether a kernel takes them (a forced
-// kernel path may refuse either), so that a refusal launches nothing.
-pme_status run_layer(const pme::RotateArgs& ra, const pme::GemmArgs& ga) {
-    pme::RotateArgs rd = ra;
-    pme::GemmArgs gd = ga;
-    rd.dry = gd.dry = true;
-    pme_status s = run_rotate(rd);
-    if (s != PME_OK) return s;
-    if ((s = run_gemm(gd)) != PME_OK) return s;
+// Rotate + quantize, then the GEMM on the codes.  On the forced matrix-core path both stages are asked first whether a kernel
+// takes them, so that a refusal launches nothing; otherwise the GEMM has a kernel for every shape.  (A dry run of the dispatch
+// costs the host 0.5 us a call, of the 10 us that bound the smallest layers.)
+template <class Gemm> pme_status run_layer(const pme::RotateArgs& ra, const Gemm& ga, pme_status (*run)(const Gemm&)) {
+    pme_status s;
+    if (g_path.load() == PME_PATH_MFMA) {
+        pme::RotateArgs rd = ra;
+        Gemm gd = ga;
+        rd.dry = gd.dry = true;
+        if ((s = run_rotate(rd)) != PME_OK || (s = run(gd)) != PME_OK) return s;
+    }
     if ((s = run_rotate(ra)) != PME_OK) return s;
-    return run_gemm(ga);
+    return run(ga);
 }
 
 }  // namespace
@@ -322,7 +327,7 @@ pme_status pme_expanded_linear(const void* x, pme_dtype xt, int64_t T, int64_t d
     float* sx = reinterpret_cast<float*>(qx + round_up((size_t)T * (size_t)(d_e / 2), 256));
     pme::RotateArgs ra{x, xt, T, d, ldx, d_e, b, k, qx, sx, nullptr, nullptr, nullptr, (hipStream_t)stream};
     pme::GemmArgs ga{qx, qw, sx, sw, nullptr, nullptr, T, d_e, N, y_bf16, ldy, false, (hipStream_t)stream};
-    return run_layer(ra, ga);
+    return run_layer(ra, ga, run_gemm);
 }
 
 pme_status pme_expanded_linear_static(const void* x, pme_dtype xt, int64_t T, int64_t d, int64_t ldx,
@@ -344,7 +349,7 @@ pme_status pme_expanded_linear_static(const void* x, pme_dtype xt, int64_t T, in
     float* sx = reinterpret_cast<float*>(qx + round_up((size_t)T * (size_t)(d_e / 2), 256));
     pme::RotateArgs ra{x, xt, T, d, ldx, d_e, b, k, qx, sx, nullptr, nullptr, nullptr, (hipStream_t)stream};
     pme::GemmArgs ga{qx, qw, sx, sw, nullptr, nullptr, T, d_e, N, y_bf16, ldy, false, (hipStream_t)stream};
-    return run_layer(ra, ga);
+    return run_layer(ra, ga, run_gemm);
 }
 
 pme_status pme_expanded_linear_asym(const void* x, pme_dtype xt, int64_t T, int64_t d, int64_t ldx,
@@ -368,7 +373,7 @@ pme_status pme_expanded_linear_asym(const void* x, pme_dtype xt, int64_t T, int6
     int32_t* zx = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(sx) + round_up(scales, 256));
     pme::RotateArgs ra{x, xt, T, d, ldx, d_e, b, k, qx, sx, zx, nullptr, nullptr, (hipStream_t)stream};
     pme::GemmArgs ga{qx, qw, sx, sw, zx, wsum, T, d_e, N, y_bf16, ldy, false, (hipStream_t)stream};
-    return run_layer(ra, ga);
+    return run_layer(ra, ga, run_gemm);
 }
 
 pme_status pme_hadamard_expand_quant_mxfp4(const void* x, pme_dtype xt, int64_t T, int64_t d, int64_t ldx,
@@ -412,14 +417,7 @@ pme_status pme_expanded_linear_mxfp4(const void* x, pme_dtype xt, int64_t T, int
     uint8_t* ex = qx + round_up((size_t)T * (size_t)(d_e / 2), 256);
     pme::RotateArgs ra{x, xt, T, d, ldx, d_e, b, k, qx, nullptr, nullptr, ex, nullptr, (hipStream_t)stream};
     pme::MxGemmArgs ga{qx, ex, qw, ew, T, d_e, N, y_bf16, ldy, (hipStream_t)stream};
-    // both stages are asked first whether a kernel takes them, so that a refusal launches nothing
-    pme::RotateArgs rd = ra;
-    pme::MxGemmArgs gd = ga;
-    rd.dry = gd.dry = true;
-    if ((s = run_rotate(rd)) != PME_OK || (s = run_mxgemm(gd)) != PME_OK) return s;
-    s = run_rotate(ra);
-    if (s != PME_OK) return s;
-    return run_mxgemm(ga);
+    return run_layer(ra, ga, run_mxgemm);
 }
 
 pme_status pme_factor_order(int64_t d_e, int32_t* b, int32_t* k) {

@@ -37,12 +37,13 @@ struct MxGemmArgs {
     hipStream_t stream;
     bool dry = false;    // only answer whether a kernel takes the shape: nothing is launched
     const char** plan = nullptr;   // dry runs: receives the name of the kernel configuration that would run
+    int tile = 0;        // few tokens: the tile estimated fastest, chosen on the way (0: not yet)
 };
 pme_status launch_mxgemm_generic(const MxGemmArgs& a);
 pme_status launch_mxgemm_mfma(const MxGemmArgs& a);
 pme_status launch_mxgemm_decode(const MxGemmArgs& a);
 pme_status launch_mxgemm_kslice(const MxGemmArgs& a, int tile);       // 0 .. 5: 8 x 32, 16 x 32, 32 x 32, 64 x 32, 64 x 64, 32 x 32 with 64-byte rows
-bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N);               // the weight-streaming kernel is estimated fastest
+bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N, int* tile);    // the weight-streaming kernel is estimated fastest; else the tile that is, where it was looked for
 
 struct GemmArgs {
     const uint8_t* qx;
@@ -58,6 +59,8 @@ struct GemmArgs {
     hipStream_t stream;
     bool dry = false;    // only answer whether a kernel takes the shape: nothing is launched
     const char** plan = nullptr;   // dry runs: receives the name of the kernel configuration that would run
+    int ksplit = -2;     // few tokens: the K-split tile estimated fastest, chosen on the way (-2: not yet, -1: none)
+    double ksplit_us = 0;
 };
 
 // Each launcher returns PME_ERR_UNSUPPORTED_PATH when the shape is outside what its kernels cover.
@@ -66,14 +69,22 @@ pme_status launch_rotate_mfma(const RotateArgs& a);
 pme_status launch_gemm_generic(const GemmArgs& a);
 pme_status launch_gemm_mfma(const GemmArgs& a);
 pme_status launch_gemm_decode(const GemmArgs& a);
-// the K-split kernel: tiles 0 .. kKsliceTiles - 1 (32 x 32, 64 x 32, 64 x 64, 96 x 64, 128 x 64, 128 x 128).  It takes d_e of
-// 1024 and more; the automatic choice uses it where it was timed (1024 .. 32768).
-constexpr int kKsliceTiles = 6;
+// the K-split kernel: tiles 0 .. kKsliceTiles - 1 (32 x 32, 64 x 32, 64 x 64, 96 x 64, 128 x 64, 128 x 128; of whole steps of 256 codes
+// only 8 x 32 and 16 x 32).  It takes d_e of 1024 and more; the automatic choice uses it where it was timed (1024 .. 32768).
+constexpr int kKsliceTiles = 8;
+// Estimated us of a GEMM on `tiles` tiles of a kernel whose fitted coefficients are c: c0 + c1 further rounds + steps (c2 + c3 first
+// round's fill + c4 further fill + c5 further rounds + c6 channels / 4096) + c7 outputs / 10^6, K in steps of 128 codes, a round one
+// workgroup on each of the 256 compute units.
+inline double tile_cost(const double (&c)[8], int64_t tiles, int64_t T, int64_t N, int64_t d_e) {
+    const double steps = (double)(d_e / 128), fill = (double)tiles / 256.0, more = fill > 1.0 ? (double)((tiles + 255) / 256 - 1) : 0.0;
+    return c[0] + c[1] * more + steps * (c[2] + c[3] * (fill < 1.0 ? fill : 1.0) + c[4] * (fill > 1.0 ? fill - 1.0 : 0.0) + c[5] * more + c[6] * (double)N / 4096.0) +
+           c[7] * 1e-6 * (double)T * (double)N;
+}
 inline bool kslice_range(int64_t d_e) { return d_e >= 1024 && d_e <= 32768; }
 pme_status launch_gemm_kslice(const GemmArgs& a, int tile);
 double decode_cost(int64_t T, int64_t N, int64_t d_e);                // estimated us
 double loader64_cost(int64_t T, int64_t N, int64_t d_e);
-int kslice_choice(int64_t T, int64_t N, int64_t d_e, double other);   // tile, or -1: not faster than `other` us
+int kslice_choice(int64_t T, int64_t N, int64_t d_e, double other, double* us = nullptr);   // tile (and its estimate), or -1: not faster than `other` us
 pme_status launch_weight_rowsum(const uint8_t* qw, int64_t N, int64_t d_e, int32_t* wsum, hipStream_t s);
 pme_status launch_pack_int4(const int8_t* codes, int64_t pairs, uint8_t* packed, hipStream_t s);
 pme_status launch_probe_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
@@ -83,6 +94,7 @@ pme_status launch_probe_empty(hipStream_t s);
 constexpr int kProbeMfmaBlocks = 512;   // workgroups of 256 threads the matrix-core probe launches
 pme_status launch_probe_mfma(int kind, int32_t* out, int iters, hipStream_t s);
 void set_gemm_tile_override(int id);
+int tile_override();
 void set_rotate_tpw_override(int tpw);
 void set_mxgemm_tile_override(int id);
 

@@ -365,6 +365,36 @@ def test_gemm_k_split_tiles(tile, d_e):
         pme.set_gemm_tile(0)
 
 
+# Steps of whole 128-byte lines (d_e a multiple of 256 that gives every wave one), and the tiles of 8 and 16 tokens (35, 36), which
+# take nothing else: one step a wave, shares that differ by one, two and three rounds of the ring; T and N around the tiles' edges.
+@pytest.mark.parametrize("d_e", (2048, 2304, 4352, 6144))
+@pytest.mark.parametrize("tile", range(29, 37))
+def test_gemm_k_split_tiles_on_whole_lines(tile, d_e):
+    bm, bn = (K_SPLIT_TILES + ((8, 32), (16, 32)))[tile - 29]
+    pme.set_path(MFMA)
+    rng = np.random.default_rng(tile * d_e)
+    for T, N in ((1, 8), (bm, bn), (bm + 1, bn + 5), (2 * bm - 1, 2 * bn + 8)):
+        qx = rng.integers(-8, 8, (T, d_e)).astype(np.int8)
+        qw = rng.integers(-8, 8, (N, d_e)).astype(np.int8)
+        sx, sw = rng.uniform(0.01, 1.0, T).astype(np.float32), rng.uniform(0.001, 0.01, N).astype(np.float32)
+        zx = rng.integers(0, 16, T).astype(np.int32)
+        acc = oracle.int_gemm(qx, qw)
+        qxd, qwd = pme.pack_int4(torch.from_numpy(qx)), pme.pack_int4(torch.from_numpy(qw))
+        sxd, swd = torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
+        pme.set_gemm_tile(tile)
+        assert pme.gemm_plan(T, d_e, N).startswith("k_gemm_decode" if bm < 32 else f"k_gemm_kslice<{bm}, {bn}, ")
+        assert np.array_equal(pme.w4a4_gemm_i32(qxd, qwd).cpu().numpy(), acc)
+        y = torch.full((T + 1, N + 3), 9.0, dtype=torch.bfloat16, device="cuda")
+        pme.w4a4_gemm(qxd, sxd, qwd, swd, y[:T, :N])
+        check_bf16(y[:T, :N].float().cpu().numpy(), oracle.dequant_bf16(acc, sx, sw))
+        assert bool((y[:, N:] == 9.0).all()) and bool((y[T] == 9.0).all())
+        wsum = pme.weight_rowsum(qwd)
+        ya = pme.w4a4_gemm_asym(qxd ^ 0x88, sxd, torch.from_numpy(zx).cuda(), qwd, swd, wsum)
+        ref = acc + (8 - zx.astype(np.int64))[:, None] * qw.astype(np.int64).sum(1)[None, :]
+        check_bf16(ya.float().cpu().numpy(), oracle.dequant_bf16(ref, sx, sw))
+        pme.set_gemm_tile(0)
+
+
 @pytest.mark.parametrize("tile", range(29, 35))
 def test_gemm_k_split_extreme_sums(tile):
     # the largest x256 accumulators that the matrix-core kernels admit: (-8) (-8) at every step of the longest K
