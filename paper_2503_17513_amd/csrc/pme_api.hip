@@ -175,6 +175,12 @@ template <class Gemm> pme_status run_layer(const pme::RotateArgs& ra, const Gemm
         rd.dry = gd.dry = true;
         if ((s = run_rotate(rd)) != PME_OK || (s = run(gd)) != PME_OK) return s;
     }
+    if constexpr (std::is_same_v<Gemm, pme::GemmArgs>) {
+        if (g_path.load() != PME_PATH_GENERIC && !pme::tile_override()) {
+            s = pme::launch_layer_token(ra, ga);
+            if (s != PME_ERR_UNSUPPORTED_PATH) return s;
+        }
+    }
     if ((s = run_rotate(ra)) != PME_OK) return s;
     return run(ga);
 }

@@ -66,6 +66,12 @@ struct GemmArgs {
 // Each launcher returns PME_ERR_UNSUPPORTED_PATH when the shape is outside what its kernels cover.
 pme_status launch_rotate_generic(const RotateArgs& a);
 pme_status launch_rotate_mfma(const RotateArgs& a);
+// The rotation's folding of butterfly stages into the base block (b, k and fold of `a` change), and the device table of the folded
+// block's fragments: fragment (tile, ks) is 1 KB at tile * stride + ks.
+void fold_stages(RotateArgs& a);
+const void* rotate_table(const RotateArgs& a, int rows, int* stride, pme_status* st);
+// The int4 layer of one token in one kernel.
+pme_status launch_layer_token(const RotateArgs& ra, const GemmArgs& ga);
 pme_status launch_gemm_generic(const GemmArgs& a);
 pme_status launch_gemm_mfma(const GemmArgs& a);
 pme_status launch_gemm_decode(const GemmArgs& a);

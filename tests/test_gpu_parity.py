@@ -952,3 +952,30 @@ def test_probe_copy():
     dst = torch.zeros_like(src)
     pme.probe_copy(src, dst)
     assert torch.equal(src, dst)
+
+
+# One token through the layer in one kernel: bit for bit what the two kernels give.  Blocks of 64 and of 128 columns (with a folded
+# one), channels around the workgroup's 16 and the limit of 4096, inputs that end inside a base row and in the first row of the
+# last K step of the block, every kind of token the range can meet.
+@pytest.mark.parametrize("d,d_e", ((8192, 8448), (8184, 8960), (6152, 9728), (8192, 9728), (8192, 8704), (4104, 8704), (8192, 10240)))
+@pytest.mark.parametrize("N", (1, 16, 250, 4096, 4097))
+def test_one_token_layer_equals_the_two_kernels(d, d_e, N):
+    g = torch.Generator(device="cuda").manual_seed(d_e + N)
+    qw = torch.randint(0, 256, (N, d_e // 2), dtype=torch.uint8, device="cuda", generator=g)
+    sw = torch.rand((N,), device="cuda", generator=g) * 0.01 + 0.001
+    wsum = pme.weight_rowsum(qw)
+    base = torch.randn((1, d), device="cuda", generator=g)
+    base[:, ::97] *= 50
+    one_sided = base.abs()
+    infinite = base.clone()
+    infinite[0, 5] = float("inf")
+    for x in (base, torch.zeros_like(base), one_sided, -one_sided, infinite):
+        x = x.to(torch.bfloat16)
+        qx, sx = pme.hadamard_expand_quant(x, d_e)
+        guard = torch.full((2, N + 3), 9.0, dtype=torch.bfloat16, device="cuda")
+        y = pme.expanded_linear(x, d_e, qw, sw, guard[:1, :N])
+        assert torch.equal(y.view(torch.int16), pme.w4a4_gemm(qx, sx, qw, sw).view(torch.int16))
+        assert bool((guard[0, N:] == 9.0).all()) and bool((guard[1] == 9.0).all())
+        qx, sx, zx = pme.hadamard_expand_quant_asym(x, d_e)
+        y = pme.expanded_linear_asym(x, d_e, qw, sw, wsum)
+        assert torch.equal(y.view(torch.int16), pme.w4a4_gemm_asym(qx, sx, zx, qw, sw, wsum).view(torch.int16))
