@@ -530,9 +530,15 @@ double kslice_cost(int64_t T, int64_t N, int64_t d_e, int tile) {
     if (lines_range(d_e)) {
         const auto& k = kLinesCosts[tile];
         const int64_t tiles = ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
-        // 8 or 16 tokens fill one row of their tiles, and only up to 4096 channels: beyond, 32 x 32 is within 3 %.  Two rounds of
-        // 32 x 32 up to 32 tokens; above, larger tiles are as fast and vary less (267 x 1731 x 15360: 11 % slower on two rounds).
-        if (tile >= 6 ? T > k.bm || N > 4096 : tiles > (tile == 0 && T <= 32 ? 512 : 256)) return 1e30;
+        // 8 or 16 tokens fill one row of their tiles, and only up to 4096 channels: beyond, 32 x 32 is within 3 %.  Weights that come
+        // from memory, and not from the caches as in the fit, slow these tiles more than the streaming kernel, which has all of them on
+        // the way at once: their time over its in the mean of 3600 layers, from the caches / from memory, is 0.87 / 1.00 from d_e = 11000
+        // on, 0.88 / 1.01 below with more than 8 tokens, but 0.94 / 1.04 with up to 8, which therefore stream; 32 x 32 for up to 16
+        // tokens 0.96 / 1.09.
+        if (tile >= 6 && (T > k.bm || N > 4096 || (T <= 8 && d_e < 11000))) return 1e30;
+        // Two rounds of 32 x 32 up to 32 tokens; above, larger tiles are as fast and vary less (267 x 1731 x 15360: 11 % slower on two).
+        if (tile < 6 && tiles > (tile == 0 && T <= 32 ? 512 : 256)) return 1e30;
+        if (tile == 0 && T <= 16 && N <= 4096) return 1e30;
         return tile_cost(k.c, tiles, T, N, d_e);
     }
     if (tile > 5) return 1e30;

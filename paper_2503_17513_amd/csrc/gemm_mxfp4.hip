@@ -539,6 +539,11 @@ bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N, int* tile) {
     // the streaming kernel reads every token's codes once per 16 channels: at most 32 tokens, and 16 where there are many channels
     if (T > 32 || (T > 16 && N >= 8192)) return false;
     if (d_e < 1024 || d_e % 128) return true;
+    // Weights that come from memory, and not from the caches as in the fit, slow the K-split tiles more than the streaming kernel,
+    // which has all of them on the way at once.  Their time over its, from the caches / from memory, in the mean of 1900 layers: from
+    // d_e = 11000 on 0.78 / 1.00; below with more than 8 tokens 0.80 / 1.02, with 2 .. 8 by less than 2048 channels 0.83 / 1.09, by more
+    // 0.91 / 1.10 and with one token 0.89 / 1.14: the last two stream, up to the 4096 channels of one round.
+    if (d_e < 11000 && T <= 8 && N <= 4096 && (T == 1 || N >= 2048)) return true;
     double us;
     *tile = mx_choice(T, d_e, N, &us);
     return us > 0.96 * mx_decode_cost(T, d_e, N);
