@@ -29,8 +29,9 @@
  *    table).
  *  - Arguments are validated on the host before any HIP call.  A status other than
  *    PME_OK means nothing was launched (PME_ERR_HIP excepted: a launch was refused by
- *    the runtime); the fused pme_expanded_linear* calls ask both of their stages whether a
- *    kernel takes the shape before they launch the first.  No C++ exception crosses this boundary.
+ *    the runtime): the GEMM has a kernel for every shape, and where the matrix-core path is forced the fused
+ *    pme_expanded_linear* calls ask both of their stages whether a kernel takes the shape before they launch
+ *    the first.  No C++ exception crosses this boundary.
  *  - Packed int4: byte j/2 of a row holds code j (even j) in its low nibble and code
  *    j+1 in its high nibble, each a 4-bit two's-complement integer (unsigned 0..15 for
  *    the asymmetric activation variant).

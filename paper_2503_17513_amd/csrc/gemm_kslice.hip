@@ -13,8 +13,8 @@
 // lines and gets half the rate.  Where d_e is a multiple of 256 and LDS has room a step is 256 codes, whole lines.  Layers, half
 // and whole lines, us (three sets of operands in turn): 32 x 4096 x 15360 17.9 and 15.0, 517 x 2048 x 8704 25.2 and 22.5, 1673 x 896 x
 // 22016 73.3 and 66.8, 48 x 6144 x 8704 14.9 and 13.9, 463 x 640 x 18432 25.0 and 22.7; 333 x 2048 x 9728 19.0 either way.  Few tokens,
-// weight-streaming kernel and 8 or 16 x 32 of whole lines: 8 x 2048 x 8448 10.1 and 9.3, 8 x 1088 x 22016 18.6 and 15.3, 16 x 2048 x 8704
-// 11.0 and 9.6.  Consecutive steps of one wave instead of every NW-th: 2-5 % slower.
+// weight-streaming kernel and 8 or 16 x 32 of whole lines: 8 x 1088 x 22016 18.6 and 15.3, 12 x 2048 x 8704 10.9 and 9.8; 8 x 2048 x 8448
+// 10.1 and 9.3, but 10.5 and 10.8 with weights from memory.  Consecutive steps of one wave instead of every NW-th: 2-5 % slower.
 // Operands, unpacking (a nibble in the top of a byte is 16 x its value), fragment layout and epilogue as in gemm_mfma.hip.
 #include "gemm_tile.h"
 
@@ -576,8 +576,8 @@ double loader64_cost(int64_t T, int64_t N, int64_t d_e) {
     return 3.76 + 0.74 * rounds + steps * (0.1616 + 0.0250 * std::min(fill, 1.0) + 0.0882 * std::max(fill - 1.0, 0.0) + 0.0381 * rounds);
 }
 
-// The K-split tile that is estimated to beat `other` us by more than 4 %, or -1.  Its time over that of the kernel it replaces,
-// on the 3900 fitted outputs of up to 6144 channels: from the caches 0.92 in the mean up to 16 tokens, 0.61 up to 64 and 0.72
+// The K-split tile that is estimated to beat `other` us by more than 4 %, or -1.  With half lines its time over that of the kernel
+// it replaces, on 3900 fitted outputs of up to 6144 channels: from the caches 0.92 in the mean up to 16 tokens, 0.61 up to 64 and 0.72
 // above, beyond 1.03 on 30 outputs; from memory 0.98, 0.82 and 0.79, beyond 1.03 on one output in ten (mostly 12 .. 32 tokens
 // by less than 2048 channels, up to 1.28, where it gains 30 % from the caches).
 int kslice_choice(int64_t T, int64_t N, int64_t d_e, double other, double* us_out) {

@@ -56,7 +56,7 @@ template <int AR, int BN, int NW, int RB, int NSTAGE> __device__ __forceinline__
     constexpr int CH = ROWS / RPB;                // code DMA instructions per stage
     constexpr int H = RB / 64;                    // units of 128 codes (two sub-steps of the matrix instruction) per K step
     static_assert(H == 1 || H == 2, "64- or 128-byte rows");
-    constexpr int SCH = mx_kslice_scale_blocks(AR, BN);          // scale DMA instructions per group of four steps
+    constexpr int SCH = mx_kslice_scale_blocks(AR, BN);          // scale DMA instructions per group of four units
     constexpr int STAGE = ROWS * RB, SCALES = NSTAGE * STAGE, GROUP = SCH * 1024, RING = mx_kslice_ring(AR, BN, RB, NSTAGE);
     static_assert(NSTAGE <= (H == 1 ? 4 : 3), "a group of scales issued with unit 4 g must have landed before unit 4 g + 3");
     constexpr int NBLK = FM * FN, ROUNDS = (NBLK + 3) / 4;

@@ -314,3 +314,10 @@ def test_rotation_and_k_split_kernels_use_no_scratch():
     kernels = [k for k in _kernel_metadata() if "k_rotate_mfma" in k[".name"] or "k_gemm_kslice" in k[".name"]]
     assert len(kernels) > 100
     assert not [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]
+
+
+def test_one_token_and_k_split_decode_kernels_use_no_scratch():
+    # the token's values, the fetched weights and the accumulators stay in registers
+    kernels = [k for k in _kernel_metadata() if any(n in k[".name"] for n in ("TokenArgs", "KSliceArgs", "MxSliceArgs"))]
+    assert len(kernels) >= 4 + 6 + 6
+    assert not [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]
