@@ -606,7 +606,10 @@ pme_status launch_gemm_mfma(const GemmArgs& a) {
             const double best = std::min(std::min(c256, c16), std::min(c192, c128));
             if (best == c256) id = wide ? 11 : 8;
             else if (best == c16) id = wide ? 16 : 2;
-            else if (best == c192) id = tiles(128, 192) <= cus ? (wide ? 28 : 21) : 9;     // the loader's registers allow one workgroup per unit
+            // beyond one round two workgroups without loader share a unit (the loader's registers allow one); not so asymmetric codes,
+            // whose waves flip the sign bit of every nibble of the tokens as well: on two rounds the loader tile is faster there, 3 to
+            // 9 % on each of 110 outputs of up to 6144 channels (layer 1959 x 4672 x 22016 9 %, 3726 x 2816 x 8448 4 %; symmetric codes 1 % slower)
+            else if (best == c192) id = wide && tiles(128, 192) <= (a.zx ? 2 * cus : cus) ? 28 : tiles(128, 192) <= cus ? 21 : 9;
             // one round of 128 x 128: four waves that split K beat four quarters of the tile with a loader wave where units
             // stay idle (us from the caches / from memory: 700 x 4096 x 8704 32.6 / 33.3 and 29.8 / 31.4; at d_e = 4352 they lose
             // 2 / 6 %) or K is long enough for the sum of the partial tiles, about 2 us, not to count (1024 x 4096 x 15360
