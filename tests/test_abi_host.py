@@ -321,3 +321,19 @@ def test_one_token_and_k_split_decode_kernels_use_no_scratch():
     kernels = [k for k in _kernel_metadata() if any(n in k[".name"] for n in ("TokenArgs", "KSliceArgs", "MxSliceArgs"))]
     assert len(kernels) >= 4 + 6 + 6
     assert not [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]
+
+
+# (T, d_e, N, variant) on either side of the lines of the choice that the fitted times draw
+FITTED_PLANS = [
+    # two rounds of 128 x 192: with asymmetric codes the loader tile (141 us shared, 129 so)
+    (3000, 8960, 3300, 1, "k_gemm_mfma<128, 192, 2, 2, 128, 3, 1, 1, true>"), (3000, 8960, 3300, 0, "k_gemm_mfma<128, 192, 2, 2, 64, 3, 0, 1, false>"),
+    # MXFP4 by 64 x 64 tiles of a shared K loop before: 25 us and 18.8 so, 35 and 16
+    (333, 9728, 2048, 2, "k_mxgemm_kslice<64, 64, "), (78, 15360, 704, 2, "k_mxgemm_"), (4096, 15360, 4096, 2, "k_mxgemm_mfma<256, 256, 2, 2, "),
+    (2048, 8704, 2048, 2, "k_mxgemm_mfma<128, 128, "), (300, 512, 256, 2, "k_mxgemm_mfma<64, 64, 2, 2, 64, 3, true>"),
+    (12, 8704, 2048, 2, "k_mxgemm_decode"), (33, 2176, 704, 2, "k_mxgemm_"), (5, 15360, 1024, 0, "k_gemm_decode"),
+]
+
+
+@pytest.mark.parametrize("T,d_e,N,variant,kernel", FITTED_PLANS)
+def test_gemm_plan_by_fitted_times(T, d_e, N, variant, kernel):
+    assert pme.gemm_plan(T, d_e, N, variant=variant).startswith(kernel)
