@@ -191,7 +191,9 @@ pme_status launch_layer_token(const RotateArgs& ra, const GemmArgs& ga) {
     pme_status st = PME_OK;
     int stride = 0;
     const void* table = rotate_table(f, rows, &stride, &st);
-    if (!table) return st;
+    // without a table (a shape that is captured cold, a full pool) the two kernels answer: some rows, such as those of a pitch that
+    // the matrix-core rotation does not take, go through the plain one, which needs no table
+    if (!table) return PME_ERR_UNSUPPORTED_PATH;
     const double gamma = 1.0 / sqrt((double)ra.d_e);
     const TokenArgs a{static_cast<const uint16_t*>(ra.x), (int)ra.d, (int)ra.d_e, f.b, static_cast<const u32x4*>(table), stride,
                       (float)(gamma / (ga.zx ? 15.0 : 7.0)), ga.qw, ga.sw, ga.wsum, (int)ga.N, static_cast<uint16_t*>(ga.y)};

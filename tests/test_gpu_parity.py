@@ -849,6 +849,46 @@ def test_first_use_of_a_shape_under_graph_capture_is_refused_and_the_capture_sur
     assert torch.equal(qx, want_q) and torch.equal(sx, want_s)
 
 
+# Base-row counts that no other test uses (55 of order 72, 118 of order 132), so that the tables are cold.  A row pitch that is no
+# multiple of 8 sends the rotation to the plain kernel, which needs no table, so the layer is captured; otherwise it is refused,
+# leaves the capture intact, and is captured once it is warm.
+@pytest.mark.parametrize("d,d_e,pitch,refused", [(7000, 9216, 7003, False), (7552, 8448, 7552, True)])
+def test_one_token_layer_captured_cold(d, d_e, pitch, refused):
+    N = 300
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((2, pitch), device="cuda", generator=g).to(torch.bfloat16)[:1, :d]
+    qw = torch.randint(0, 256, (N, d_e // 2), dtype=torch.uint8, device="cuda", generator=g)
+    sw = torch.rand((N,), device="cuda", generator=g) * 0.01 + 0.001
+    y = torch.zeros((1, N), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty((pme.workspace_bytes(1, d, d_e, N),), dtype=torch.uint8, device="cuda")
+    marker = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    graph, status = torch.cuda.CUDAGraph(), 0
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        marker.add_(1.0)
+        try:
+            pme.expanded_linear(x, d_e, qw, sw, y, ws)
+        except pme.PmeError as e:
+            status = e.status
+    assert status == (9 if refused else 0)
+    if refused:
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(marker[0]) == 1.0 and not bool(y.any())
+    want = pme.w4a4_gemm(*pme.hadamard_expand_quant(x, d_e), qw, sw)             # warm from here on
+    if refused:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            pme.expanded_linear(x, d_e, qw, sw, y, ws)
+    for _ in range(3):
+        y.fill_(9.0)
+        ws.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+
+
 def test_fp32_rows_of_the_largest_blocks_are_captured_cold():
     # order 312 from fp32: the matrix-core kernel needs a table that a capture cannot fill, so the plain kernel is captured
     d, d_e, T = 13000, 19968, 3                     # 204 real base rows: no other test uses them
