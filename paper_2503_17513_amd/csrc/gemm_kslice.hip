@@ -418,18 +418,14 @@ template <int AR, int BN, int NW, int NSTAGE, int MODE_> __device__ __forceinlin
     });
 }
 
-template <int BM, int BN, int NW, int NSTAGE, int MODE> __global__ void __launch_bounds__(64 * NW) k_gemm_kslice(KSliceArgs a) {
-    kslice_tile<BM, BN, NW, NSTAGE, MODE>(a);
-}
-// the tiles of few tokens go by the name of the decode kernels
-template <int AR, int BN, int NW, int NSTAGE, int MODE> __global__ void __launch_bounds__(64 * NW) k_gemm_decode(KSliceArgs a) {
+template <int AR, int BN, int NW, int NSTAGE, int MODE> __global__ void __launch_bounds__(64 * NW) k_gemm_kslice(KSliceArgs a) {
     kslice_tile<AR, BN, NW, NSTAGE, MODE>(a);
 }
 
-template <int BM, int BN, int NW, int NSTAGE> const char* kslice_name(int mode) {
+template <int AR, int BN, int NW, int NSTAGE> const char* kslice_name(int mode) {
     auto make = [](int m) {
         char buf[64];
-        snprintf(buf, sizeof buf, "k_gemm_kslice<%d, %d, %d, %d, %d>", BM, BN, NW, NSTAGE, m);
+        snprintf(buf, sizeof buf, "k_gemm_kslice<%d, %d, %d, %d, %d>", AR, BN, NW, NSTAGE, m);
         return std::string(buf);
     };
     static const std::string names[7] = {make(MODE_BF16), make(MODE_ASYM), make(MODE_I32), "", make(HALF_LINES + MODE_BF16), make(HALF_LINES + MODE_ASYM),
@@ -440,20 +436,16 @@ template <int BM, int BN, int NW, int NSTAGE> const char* kslice_name(int mode) 
 template <int AR, int BN, int NW, int NSTAGE, int MODE> pme_status launch_kslice_mode(const GemmArgs& a) {
     const int kb = (int)(a.d_e / 2);
     constexpr int RB = kslice_lines(AR, BN, NSTAGE, MODE) ? 128 : 64;
-    constexpr bool FEW = AR < 32;
     if (kb % RB || kb < RB * NW) return PME_ERR_UNSUPPORTED_PATH;      // whole K steps, at least one for each wave
     if ((int64_t)std::max(a.T, a.N) * kb >= (int64_t(1) << 32)) return PME_ERR_UNSUPPORTED_PATH;   // 32-bit DMA offsets
     if (a.dry) {
-        if (a.plan) *a.plan = FEW ? "k_gemm_decode" : kslice_name<AR, BN, NW, NSTAGE>(MODE);
+        if (a.plan) *a.plan = kslice_name<AR, BN, NW, NSTAGE>(MODE);
         return PME_OK;
     }
     const int tiles_m = (int)((a.T + AR - 1) / AR), tiles_n = (int)((a.N + BN - 1) / BN);
     constexpr int lds = kslice_lds(AR, BN, NW, NSTAGE, MODE);
     static_assert(lds <= 160 * 1024, "the rings fit in LDS");
-    constexpr auto kern = [] {
-        if constexpr (FEW) return k_gemm_decode<AR, BN, NW, NSTAGE, MODE>;
-        else return k_gemm_kslice<AR, BN, NW, NSTAGE, MODE>;
-    }();
+    constexpr auto kern = k_gemm_kslice<AR, BN, NW, NSTAGE, MODE>;
     static std::atomic<uint32_t> done;
     if (lds > 64 * 1024 && allow_dynamic_lds(kern, lds, done) != PME_OK) return PME_ERR_HIP;
     const int vec = (a.N % 8 == 0 && a.ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0) ? 1 : 0;

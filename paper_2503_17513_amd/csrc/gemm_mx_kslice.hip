@@ -278,16 +278,11 @@ template <int AR, int BN, int NW, int RB, int NSTAGE> __device__ __forceinline__
 template <int AR, int BN, int NW, int RB, int NSTAGE> __global__ void __launch_bounds__(64 * NW) k_mxgemm_kslice(MxSliceArgs a) {
     mx_kslice_tile<AR, BN, NW, RB, NSTAGE>(a);
 }
-// the tiles of few tokens go by the name of the decode kernels
-template <int AR, int BN, int NW, int RB, int NSTAGE> __global__ void __launch_bounds__(64 * NW) k_mxgemm_decode(MxSliceArgs a) {
-    mx_kslice_tile<AR, BN, NW, RB, NSTAGE>(a);
-}
 
 template <int AR, int BN, int NW, int RB, int NSTAGE> pme_status launch_mx_kslice(const MxGemmArgs& a) {
     const int kb = (int)(a.d_e / 2), eb = (int)(a.d_e / 32);
     if (kb % RB || kb < RB * NW) return PME_ERR_UNSUPPORTED_PATH;      // whole K steps, at least one for each wave
     if ((int64_t)std::max(a.T, a.N) * kb >= (int64_t(1) << 32)) return PME_ERR_UNSUPPORTED_PATH;   // 32-bit DMA offsets
-    constexpr bool FEW = AR < 32;
     if (a.dry) {
         if (a.plan) {
             static const std::string name = [] {
@@ -295,17 +290,14 @@ template <int AR, int BN, int NW, int RB, int NSTAGE> pme_status launch_mx_kslic
                 snprintf(buf, sizeof buf, "k_mxgemm_kslice<%d, %d, %d, %d, %d>", AR, BN, NW, RB, NSTAGE);
                 return std::string(buf);
             }();
-            *a.plan = FEW ? "k_mxgemm_decode" : name.c_str();
+            *a.plan = name.c_str();
         }
         return PME_OK;
     }
     const int tiles_m = (int)((a.T + AR - 1) / AR), tiles_n = (int)((a.N + BN - 1) / BN);
     constexpr int lds = mx_kslice_lds(AR, BN, NW, RB, NSTAGE);
     static_assert(lds <= 160 * 1024, "the rings fit in LDS");
-    constexpr auto kern = [] {
-        if constexpr (FEW) return k_mxgemm_decode<AR, BN, NW, RB, NSTAGE>;
-        else return k_mxgemm_kslice<AR, BN, NW, RB, NSTAGE>;
-    }();
+    constexpr auto kern = k_mxgemm_kslice<AR, BN, NW, RB, NSTAGE>;
     static std::atomic<uint32_t> done;
     if (lds > 64 * 1024 && allow_dynamic_lds(kern, lds, done) != PME_OK) return PME_ERR_HIP;
     const int vec = (a.N % 8 == 0 && a.ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0) ? 1 : 0;

@@ -229,14 +229,22 @@ def test_gemm_plan_names_the_kernel_without_launching():
 
 # (T, d_e, N) and the int4 kernel that measured faster, in us from the caches / from memory
 PLANS = [
-    # few tokens by up to 4096 channels: the streaming kernel at any K (1 x 12288 x 2048: 7.6 / 7.2, K-split 9.2 / 11.2;
-    # 2 x 15360 x 3072: 9.5 / 9.3, 10.7 / 13.8; 1 x 32768 x 2048: 14.6 / 14.4, 17.2 / 24.0)
+    # few tokens by up to 4096 channels: the streaming kernel up to 8 tokens below d_e = 11000, and wherever K is no whole number of
+    # 256 codes or shorter than 8192 (8 x 10240 x 2048: 7.9 / 8.0, 8 x 32 5.9 / 7.8; 9 x 7680 x 2048: 6.2 / 6.3, 16 x 32 5.3 / 6.8)
     (1, 8448, 2048, "k_gemm_decode"), (8, 8448, 2048, "k_gemm_decode"), (4, 8704, 4096, "k_gemm_decode"),
-    (1, 12288, 2048, "k_gemm_decode"), (2, 12288, 2112, "k_gemm_decode"), (3, 15360, 1356, "k_gemm_decode"),
-    (2, 15360, 3072, "k_gemm_decode"), (1, 22016, 3072, "k_gemm_decode"), (1, 32768, 2048, "k_gemm_decode"),
+    (8, 10240, 2048, "k_gemm_decode"), (9, 7680, 2048, "k_gemm_decode"), (20, 4352, 2048, "k_gemm_decode"),
     (16, 1024, 3072, "k_gemm_decode"), (58, 1024, 5056, "k_gemm_decode"),
-    # from a second round of 4096 channels, or with more tokens, a K-split tile (1 x 12288 x 5120: 9.8 / 12.3, streaming 13.3 / 13.0;
-    # 32 x 15360 x 4096: 13.6 / 18.2, 18.8 / 19.2)
+    # up to 8 tokens from there on 8 x 32, K split (8 x 11008 x 2048: 6.1 / 7.7, streaming 7.8 / 7.9; 1 x 12288 x 2048: 6.3 / 7.6, 7.3 / 7.3;
+    # 5 x 15360 x 1024: 6.8 / 9.0, 9.3 / 9.4; 1 x 22016 x 3072: 9.4 / 12.6, 12.2 / 12.7; 1 x 32768 x 2048: 11.4 / 14.1, 14.4 / 14.5)
+    (8, 11008, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 12288, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"),
+    (2, 12288, 2112, "k_gemm_kslice<8, 32, 8, 3, 0>"), (3, 15360, 1356, "k_gemm_kslice<8, 32, 8, 3, 0>"),
+    (5, 15360, 1024, "k_gemm_kslice<8, 32, 8, 3, 0>"), (2, 15360, 3072, "k_gemm_kslice<8, 32, 8, 3, 0>"),
+    (1, 22016, 3072, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 32768, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"),
+    # 9 .. 16 tokens on 16 x 32 (9 x 8448 x 2048: 5.4 / 6.9, streaming 6.4 / 6.7; 16 x 8448 x 2048: 5.4 / 7.3, 7.2 / 7.6)
+    (9, 8448, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"), (16, 8448, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"),
+    (12, 8704, 4096, "k_gemm_kslice<16, 32, 8, 3, 0>"), (12, 8704, 4160, "k_gemm_kslice<32, 32, 8, 2, 0>"),
+    # from a second round of 4096 channels, or with more tokens, 32 x 32 and larger (1 x 12288 x 5120: 8.1 / 10.0, streaming 13.3 / 13.0;
+    # 32 x 15360 x 4096: 9.0 / 13.4, 18.8 / 19.2)
     (1, 12288, 5120, "k_gemm_kslice<32, 32, 8, 2, 0>"), (4, 8704, 6144, "k_gemm_kslice<32, 32, 8, 2, 0>"),
     (32, 15360, 4096, "k_gemm_kslice<32, 32, 8, 2, 0>"), (48, 8704, 6144, "k_gemm_kslice<64, 32, 8, 3, 0>"),
     # small outputs: each K-split tile, and the 64 x 64 tile where K is short or the tiles many
@@ -318,8 +326,12 @@ def test_rotation_and_k_split_kernels_use_no_scratch():
 
 def test_one_token_and_k_split_decode_kernels_use_no_scratch():
     # the token's values, the fetched weights and the accumulators stay in registers
-    kernels = [k for k in _kernel_metadata() if any(n in k[".name"] for n in ("TokenArgs", "KSliceArgs", "MxSliceArgs"))]
-    assert len(kernels) >= 4 + 6 + 6
+    kernels = []
+    # the one-token kernel at two widths and two quantizers; every tile of either K-split kernel
+    for args, least in (("9TokenArgs", 4), ("10KSliceArgs", 8 * 3), ("11MxSliceArgs", 6)):
+        found = [k for k in _kernel_metadata() if args in k[".symbol"]]
+        assert len(found) >= least, args
+        kernels += found
     assert not [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]
 
 
@@ -328,9 +340,10 @@ FITTED_PLANS = [
     # two rounds of 128 x 192: with asymmetric codes the loader tile (141 us shared, 129 so)
     (3000, 8960, 3300, 1, "k_gemm_mfma<128, 192, 2, 2, 128, 3, 1, 1, true>"), (3000, 8960, 3300, 0, "k_gemm_mfma<128, 192, 2, 2, 64, 3, 0, 1, false>"),
     # MXFP4 by 64 x 64 tiles of a shared K loop before: 25 us and 18.8 so, 35 and 16
-    (333, 9728, 2048, 2, "k_mxgemm_kslice<64, 64, "), (78, 15360, 704, 2, "k_mxgemm_"), (4096, 15360, 4096, 2, "k_mxgemm_mfma<256, 256, 2, 2, "),
+    (333, 9728, 2048, 2, "k_mxgemm_kslice<64, 64, 4, 128, 2>"), (78, 15360, 704, 2, "k_mxgemm_kslice<16, 32, 4, 128, 3>"),
+    (33, 2176, 704, 2, "k_mxgemm_kslice<32, 32, 4, 64, 4>"), (4096, 15360, 4096, 2, "k_mxgemm_mfma<256, 256, 2, 2, "),
     (2048, 8704, 2048, 2, "k_mxgemm_mfma<128, 128, "), (300, 512, 256, 2, "k_mxgemm_mfma<64, 64, 2, 2, 64, 3, true>"),
-    (12, 8704, 2048, 2, "k_mxgemm_decode"), (33, 2176, 704, 2, "k_mxgemm_"), (5, 15360, 1024, 0, "k_gemm_decode"),
+    (12, 8704, 2048, 2, "k_mxgemm_kslice<16, 32, 4, 128, 3>"), (130, 8704, 300, 2, "k_mxgemm_kslice<16, 32, 4, 128, 3>"),
 ]
 
 

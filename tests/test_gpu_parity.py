@@ -382,7 +382,7 @@ def test_gemm_k_split_tiles_on_whole_lines(tile, d_e):
         qxd, qwd = pme.pack_int4(torch.from_numpy(qx)), pme.pack_int4(torch.from_numpy(qw))
         sxd, swd = torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
         pme.set_gemm_tile(tile)
-        assert pme.gemm_plan(T, d_e, N).startswith("k_gemm_decode" if bm < 32 else f"k_gemm_kslice<{bm}, {bn}, ")
+        assert pme.gemm_plan(T, d_e, N).startswith(f"k_gemm_kslice<{bm}, {bn}, ")
         assert np.array_equal(pme.w4a4_gemm_i32(qxd, qwd).cpu().numpy(), acc)
         y = torch.full((T + 1, N + 3), 9.0, dtype=torch.bfloat16, device="cuda")
         pme.w4a4_gemm(qxd, sxd, qwd, swd, y[:T, :N])
@@ -409,7 +409,7 @@ def test_gemm_k_split_extreme_sums(tile):
 
 # The automatic choice on either side of its lines: few tokens, small outputs, one round of 128 x 128.
 @pytest.mark.parametrize("T,d_e,N,kernel", [
-    (2, 12288, 2112, "k_gemm_decode"), (1, 12288, 4160, "k_gemm_kslice<32, 32,"), (20, 8704, 1000, "k_gemm_kslice<32, 32,"),
+    (2, 12288, 2112, "k_gemm_kslice<8, 32,"), (8, 8704, 2048, "k_gemm_decode"), (13, 8704, 1999, "k_gemm_kslice<16, 32,"), (1, 12288, 4160, "k_gemm_kslice<32, 32,"), (20, 8704, 1000, "k_gemm_kslice<32, 32,"),
     (58, 1024, 5056, "k_gemm_decode"), (48, 8704, 6144, "k_gemm_kslice<64, 32,"), (70, 1024, 9000, "k_gemm_mfma<64, 64,"),
     (333, 9728, 1999, "k_gemm_kslice<64, 64,"), (517, 8704, 2048, "k_gemm_kslice<96, 64,"), (700, 8704, 4096, "k_gemm_kslice<128, 128,"),
     (700, 4352, 4000, "k_gemm_mfma<128, 128,")])
