@@ -265,8 +265,9 @@ pme_status pme_probe_launch(void* stream);
 pme_status pme_probe_mfma(int kind, int32_t* out, size_t out_elems, int iters, double* ops, void* stream);
 
 /* Tuning hook for benchmarks: force the MFMA GEMM's tile configuration (0 = choose from the shape;
- * 1..36 = a fixed entry of the int4 kernel's tile table, 100 + (1..21) = of the MXFP4 kernel's; 0 resets
- * both).  Process-wide, not thread-safe. */
+ * 1..36 = a fixed entry of the int4 kernel's tile table, 100 + (1..14 or 16..21) = of the MXFP4 kernel's; 0 resets
+ * both).  A shape that the forced tile does not take goes to the plain-ALU kernel, or is refused where the
+ * matrix-core path is forced too.  Process-wide, not thread-safe. */
 void pme_set_gemm_tile(int id);
 
 /* Which kernel configuration the GEMM of a T x d_e x N layer would run under the current path and tile settings,

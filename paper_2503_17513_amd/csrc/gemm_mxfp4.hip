@@ -550,6 +550,7 @@ bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N, int* tile) {
 }
 
 void set_mxgemm_tile_override(int id) { g_mx_tile_override = id; }
+int mxgemm_tile_override() { return g_mx_tile_override; }
 
 pme_status launch_mxgemm_generic(const MxGemmArgs& a) {
     if (a.dry) {

@@ -137,8 +137,8 @@ pme_status run_mxgemm_slice(pme::MxGemmArgs a) {
     if (path != PME_PATH_GENERIC) {
         const bool stream_weights = pme::mxgemm_streams(a.T, a.d_e, a.N, &a.tile);
         pme_status s = stream_weights ? pme::launch_mxgemm_decode(a) : pme::launch_mxgemm_mfma(a);
-        // the streaming kernel takes scale bytes of any alignment, the others more tokens
-        if (s == PME_ERR_UNSUPPORTED_PATH) s = stream_weights ? pme::launch_mxgemm_mfma(a) : pme::launch_mxgemm_decode(a);
+        // the streaming kernel takes scale bytes of any alignment, the others more tokens; a forced tile that refuses is not replaced
+        if (s == PME_ERR_UNSUPPORTED_PATH && !pme::mxgemm_tile_override()) s = stream_weights ? pme::launch_mxgemm_mfma(a) : pme::launch_mxgemm_decode(a);
         if (s != PME_ERR_UNSUPPORTED_PATH || path == PME_PATH_MFMA) return s;
     }
     return pme::launch_mxgemm_generic(a);

@@ -103,6 +103,7 @@ void set_gemm_tile_override(int id);
 int tile_override();
 void set_rotate_tpw_override(int tpw);
 void set_mxgemm_tile_override(int id);
+int mxgemm_tile_override();
 
 // Lets `kern` be launched with up to `bytes` of dynamic LDS.  The attribute is set once per kernel and
 // device (`done` holds one bit per device and belongs to the kernel's launcher), not on every launch.

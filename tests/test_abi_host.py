@@ -263,6 +263,22 @@ def test_gemm_plan_takes_the_faster_kernel(T, d_e, N, kernel):
     assert pme.gemm_plan(T, d_e, N, variant=1).startswith(kernel.replace(", 0>", ", 1>"))
 
 
+# shapes that a tile does not take: half a K step of 256 codes, less than a step for each wave, an id that is none
+@pytest.mark.parametrize("tile,T,d_e", [(116, 16, 1152), (116, 8, 1024), (117, 16, 1152), (118, 16, 1152), (118, 300, 1152), (101, 16, 1152),
+                                        (115, 16, 2048), (122, 16, 2048), (35, 8, 2176), (36, 16, 1024), (37, 16, 2048)])
+def test_a_forced_tile_that_refuses_is_not_replaced(tile, T, d_e):
+    variant = 2 if tile >= 100 else 0
+    f, buf = pme.lib().pme_gemm_plan, C.create_string_buffer(64)
+    try:
+        pme.set_gemm_tile(tile)
+        assert pme.gemm_plan(T, d_e, 300, variant=variant) == ("k_mxgemm_generic" if variant else "k_gemm_generic")
+        pme.set_path(pme.PATH_MFMA)
+        assert f(variant, T, d_e, 300, buf, 64) == PATH
+    finally:
+        pme.set_gemm_tile(0)
+        pme.set_path(pme.PATH_AUTO)
+
+
 def test_pack_int4_argument_errors():
     f = pme.lib().pme_pack_int4
     assert f(None, 4, 8, FAKE, None) == NULL

@@ -155,6 +155,7 @@ def test_mxfp4_gemm_k_split_tiles(tile, d_e):
     pme.set_path(MFMA)
     pme.set_gemm_tile(100 + tile)
     for T, N in ((1, 8), (bm, bn), (bm + 1, bn + 8), (2 * bm - 1, 2 * bn + 3)):
+        assert pme.gemm_plan(T, d_e, N, variant=2).startswith("k_mxgemm_kslice<%d, %d, %d, %d, " % KSPLIT[tile])
         qx = rng.integers(0, 16, size=(T, d_e), dtype=np.uint8)
         qw = rng.integers(0, 16, size=(N, d_e), dtype=np.uint8)
         ex = rng.integers(112, 136, size=(T, d_e // 32), dtype=np.uint8)
