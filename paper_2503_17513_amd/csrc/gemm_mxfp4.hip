@@ -531,6 +531,22 @@ int mx_choice(int64_t T, int64_t d_e, int64_t N, double* us) {
     return id;
 }
 
+// The weight-streaming kernel where the K-split tiles lose with weights from memory, and not from the caches as in the fit: a decode
+// step reads the weights of all layers, which stay in no cache.  Streaming has all of a workgroup's weights on the way at once, the
+// tiles two or three K steps of every wave.  Time of the tile that the estimates name over streaming's, from memory (largest) /
+// caches, GEMM alone with 640 MB of weights in turn and three sets, geometric means of 1500 outputs of 64 .. 16000 channels; what streams:
+//   one round of 4096 channels, whole lines: 1 token from d_e = 12288 on 1.04 (1.12) / 0.64; 2 .. 8 tokens below 12288 1.09 (1.39) /
+//   0.77; 9, 10 below 10240 and 11, 12 below 6144 1.03 (1.31) / 0.79; 13 .. 16 below 6144 1.03 (1.24) / 0.84;
+//   half lines (d_e no multiple of 256), up to 4096 channels: up to 16 tokens 1.27 (1.48) / 0.95, above 1.18 (1.46) / 0.82;
+//   more channels, up to 16 tokens: whole lines below d_e = 2560 1.09 (1.36) / 0.93, half lines below 4096 1.17 (1.42) / 0.95;
+// and what does not: 2 .. 8 tokens from 12288 on 0.95 (1.09) / 0.55, 9 .. 16 beyond the lines 0.83 (1.09) / 0.53, 17 .. 32 on whole lines
+// 0.64 (1.13) / 0.44, up to 16 tokens by more than 4096 channels beyond theirs 0.71 (1.08) / 0.57.
+bool streams_from_memory(int64_t T, int64_t d_e, int64_t N) {
+    const bool half_lines = d_e % 256 != 0;
+    if (N > 4096) return T <= 16 && d_e < (half_lines ? 4096 : 2560);
+    return half_lines || T < (d_e >= 12288 ? 2 : d_e >= 10240 ? 9 : d_e >= 6144 ? 11 : 17);
+}
+
 }  // namespace
 
 bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N, int* tile) {
@@ -539,11 +555,7 @@ bool mxgemm_streams(int64_t T, int64_t d_e, int64_t N, int* tile) {
     // the streaming kernel reads every token's codes once per 16 channels: at most 32 tokens, and 16 where there are many channels
     if (T > 32 || (T > 16 && N >= 8192)) return false;
     if (d_e < 1024 || d_e % 128) return true;
-    // Weights that come from memory, and not from the caches as in the fit, slow the K-split tiles more than the streaming kernel,
-    // which has all of them on the way at once.  Their time over its, from the caches / from memory, in the mean of 1900 layers: from
-    // d_e = 11000 on 0.78 / 1.00; below with more than 8 tokens 0.80 / 1.02, with 2 .. 8 by less than 2048 channels 0.83 / 1.09, by more
-    // 0.91 / 1.10 and with one token 0.89 / 1.14: the last two stream, up to the 4096 channels of one round.
-    if (d_e < 11000 && T <= 8 && N <= 4096 && (T == 1 || N >= 2048)) return true;
+    if (streams_from_memory(T, d_e, N)) return true;
     double us;
     *tile = mx_choice(T, d_e, N, &us);
     return us > 0.96 * mx_decode_cost(T, d_e, N);

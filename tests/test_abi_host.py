@@ -360,6 +360,19 @@ FITTED_PLANS = [
     (33, 2176, 704, 2, "k_mxgemm_kslice<32, 32, 4, 64, 4>"), (4096, 15360, 4096, 2, "k_mxgemm_mfma<256, 256, 2, 2, "),
     (2048, 8704, 2048, 2, "k_mxgemm_mfma<128, 128, "), (300, 512, 256, 2, "k_mxgemm_mfma<64, 64, 2, 2, 64, 3, true>"),
     (12, 8704, 2048, 2, "k_mxgemm_kslice<16, 32, 4, 128, 3>"), (130, 8704, 300, 2, "k_mxgemm_kslice<16, 32, 4, 128, 3>"),
+    # few tokens, MXFP4: streaming where the K-split tiles lose with weights from memory (us from the caches / from memory, streaming and
+    # K-split: 8 x 8704 x 1024 7.3 / 7.3 and 5.3 / 8.6, 8 x 11008 x 1024 8.5 / 8.6 and 5.6 / 9.9, 1 x 22016 x 2048 13.0 / 13.1 and 9.6 / 14.7,
+    # 17 x 2176 x 1024 3.9 / 3.9 and 3.9 / 5.2, 32 x 4480 x 2048 7.1 / 7.2 and 4.5 / 8.3, 1 x 2176 x 10496 5.0 / 5.1 and 5.7 / 7.5), and the
+    # other side of each line (2 x 12288 x 2048 9.5 / 9.5 and 6.7 / 9.6, 9 x 10240 x 2048 10.1 / 10.2 and 6.5 / 9.8, 8 x 4480 x 4160 7.0 / 7.1
+    # and 4.7 / 6.4, 16 x 2560 x 6144 6.2 / 6.4 and 4.1 / 5.4, 1 x 8448 x 4160 9.6 / 9.8 and 5.9 / 7.8)
+    (8, 8448, 2048, 2, "k_mxgemm_decode"), (8, 8704, 1024, 2, "k_mxgemm_decode"), (10, 8704, 2048, 2, "k_mxgemm_decode"),
+    (11, 8704, 2048, 2, "k_mxgemm_kslice<16, 32, "), (12, 5120, 1024, 2, "k_mxgemm_decode"), (11, 6144, 1024, 2, "k_mxgemm_kslice<16, 32, "),
+    (16, 4608, 2048, 2, "k_mxgemm_decode"), (17, 4608, 2048, 2, "k_mxgemm_kslice<32, 32, 4, 128, "), (8, 10240, 2048, 2, "k_mxgemm_decode"),
+    (9, 10240, 2048, 2, "k_mxgemm_kslice<16, 32, "), (8, 11008, 1024, 2, "k_mxgemm_decode"), (2, 12288, 2048, 2, "k_mxgemm_kslice<8, 32, "),
+    (1, 12288, 2048, 2, "k_mxgemm_decode"), (1, 22016, 4096, 2, "k_mxgemm_decode"), (1, 8448, 4160, 2, "k_mxgemm_kslice<16, 32, "),
+    (17, 2176, 1024, 2, "k_mxgemm_decode"), (32, 4480, 4096, 2, "k_mxgemm_decode"), (32, 4480, 4160, 2, "k_mxgemm_kslice<32, 32, 4, 64, "),
+    (8, 4480, 4160, 2, "k_mxgemm_kslice<32, 32, 4, 64, "), (8, 2176, 4160, 2, "k_mxgemm_decode"), (1, 2176, 10496, 2, "k_mxgemm_decode"),
+    (16, 2304, 6144, 2, "k_mxgemm_decode"), (16, 2560, 6144, 2, "k_mxgemm_kslice<16, 32, "), (17, 2176, 6144, 2, "k_mxgemm_kslice<32, 32, 4, 64, "),
 ]
 
 
