@@ -13,8 +13,9 @@
 // lines and gets half the rate.  Where d_e is a multiple of 256 and LDS has room a step is 256 codes, whole lines.  Layers, half
 // and whole lines, us (three sets of operands in turn): 32 x 4096 x 15360 17.9 and 15.0, 517 x 2048 x 8704 25.2 and 22.5, 1673 x 896 x
 // 22016 73.3 and 66.8, 48 x 6144 x 8704 14.9 and 13.9, 463 x 640 x 18432 25.0 and 22.7; 333 x 2048 x 9728 19.0 either way.  Few tokens,
-// weight-streaming kernel and 8 or 16 x 32 of whole lines: 8 x 1088 x 22016 18.6 and 15.3, 12 x 2048 x 8704 10.9 and 9.8; 8 x 2048 x 8448
-// 10.1 and 9.3, but 10.5 and 10.8 with weights from memory.  Consecutive steps of one wave instead of every NW-th: 2-5 % slower.
+// weight-streaming kernel and 8 or 16 x 32 of whole lines, GEMM alone, us from the caches / from memory: 8 x 1088 x 22016 12.6 / 12.7 and
+// 8.9 / 11.7, 16 x 2048 x 10240 9.0 / 9.1 and 6.2 / 8.8; but 12 x 2048 x 8704 6.9 / 6.9 and 5.2 / 7.4, which streams (see kslice_cost).
+// Consecutive steps of one wave instead of every NW-th: 2-5 % slower.
 // Operands, unpacking (a nibble in the top of a byte is 16 x its value), fragment layout and epilogue as in gemm_mfma.hip.
 #include "gemm_tile.h"
 
@@ -523,11 +524,14 @@ double kslice_cost(int64_t T, int64_t N, int64_t d_e, int tile) {
         const auto& k = kLinesCosts[tile];
         const int64_t tiles = ((T + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
         // 8 or 16 tokens fill one row of their tiles, and only up to 4096 channels: beyond, 32 x 32 is within 3 %.  Weights that come
-        // from memory, and not from the caches as in the fit, slow these tiles more than the streaming kernel, which has all of them on
-        // the way at once: their time over its in the mean of 3600 layers, from the caches / from memory, is 0.87 / 1.00 from d_e = 11000
-        // on, 0.88 / 1.01 below with more than 8 tokens, but 0.94 / 1.04 with up to 8, which therefore stream; 32 x 32 for up to 16
-        // tokens 0.96 / 1.09.
-        if (tile >= 6 && (T > k.bm || N > 4096 || (T <= 8 && d_e < 11000))) return 1e30;
+        // from memory, as a decode step reads them, and not from the caches as in the fit, slow these tiles more than the streaming kernel,
+        // which has all of them on the way at once.  Their time over its, from the caches / from memory (largest), GEMM alone, three sets
+        // and 700 MB of weights in turn, geometric means of 1500 outputs of 400 .. 4096 channels; what streams, all that lost more than 5 %:
+        //   1 token below d_e = 15000 0.90 / 1.09 (1.12), 2 .. 4 0.86 / 1.06 (1.11); 9 .. 12 below 10000 0.84 / 1.08 (1.16);
+        // and what does not: up to 4 tokens from 15000 on 0.80 / 0.98 (1.06); 5 .. 8 below 15000 0.82 / 1.04 (1.07), from there on 0.74 / 0.95;
+        // 9 .. 12 from 10000 on 0.72 / 0.97 (1.06); 13 .. 16 below 10000 0.78 / 1.04 (1.10), from there on 0.66 / 0.93.
+        const int64_t least = T <= 4 ? 15000 : T <= 8 ? 11000 : T <= 12 ? 10000 : 0;
+        if (tile >= 6 && (T > k.bm || N > 4096 || d_e < least)) return 1e30;
         // Two rounds of 32 x 32 up to 32 tokens; above, larger tiles are as fast and vary less (267 x 1731 x 15360: 11 % slower on two).
         if (tile < 6 && tiles > (tile == 0 && T <= 32 ? 512 : 256)) return 1e30;
         if (tile == 0 && T <= 16 && N <= 4096) return 1e30;

@@ -92,9 +92,9 @@ pme_status run_gemm_slice(pme::GemmArgs a) {
     int path = g_path.load();
     if (path != PME_PATH_GENERIC) {
         // few tokens: the weight-streaming kernel while the output has fewer than 128 tiles of 64 x 64, unless a K-split tile
-        // is estimated faster: from two rounds of 4096 channels on, with more than 8 tokens, whose codes the streaming kernel
-        // reads once per 16 channels, and from d_e = 11000 on (layers, us, streaming and K-split: 8 x 1088 x 22016 18.6 and 15.3,
-        // 12 x 2048 x 8704 10.9 and 9.8, 5 x 1024 x 15360 13.7 and 11.9)
+        // is estimated faster: from two rounds of 4096 channels on, with more than 12 tokens, whose codes the streaming kernel
+        // reads once per 16 channels, and with fewer at long K (GEMM, us from the caches / from memory, streaming and K-split:
+        // 8 x 1088 x 22016 12.6 / 12.7 and 8.9 / 11.7, 16 x 2048 x 10240 9.0 / 9.1 and 6.2 / 8.8, 5 x 1024 x 15360 9.0 / 9.1 and 6.6 / 9.1)
         bool stream_weights = !pme::tile_override() && (a.T <= 16 || (a.T <= 64 && a.N < 8192));
         if (stream_weights) {
             a.ksplit = pme::kslice_choice(a.T, a.N, a.d_e, pme::decode_cost(a.T, a.N, a.d_e), &a.ksplit_us);

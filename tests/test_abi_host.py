@@ -229,22 +229,24 @@ def test_gemm_plan_names_the_kernel_without_launching():
 
 # (T, d_e, N) and the int4 kernel that measured faster, in us from the caches / from memory
 PLANS = [
-    # few tokens by up to 4096 channels: the streaming kernel up to 8 tokens below d_e = 11000, and wherever K is no whole number of
-    # 256 codes or shorter than 8192 (8 x 10240 x 2048: 7.9 / 8.0, 8 x 32 5.9 / 7.8; 9 x 7680 x 2048: 6.2 / 6.3, 16 x 32 5.3 / 6.8)
+    # few tokens by up to 4096 channels: the streaming kernel up to 4 below d_e = 15000, up to 8 below 11000 and up to 12 below 10000, where
+    # the K-split tiles lose with weights from memory, and wherever K is no whole number of 256 codes or shorter than 8192 (streaming
+    # and 8 or 16 x 32: 1 x 12288 x 2048 7.0 / 7.1 and 6.5 / 7.8, 2 x 14848 x 2048 8.2 / 8.2 and 7.1 / 8.7, 10 x 8448 x 2048 6.4 / 6.5 and
+    # 5.2 / 7.1, 12 x 8704 x 4096 7.4 / 7.5 and 6.2 / 7.9, 12 x 8704 x 2048 6.9 / 6.9 and 5.2 / 7.4)
     (1, 8448, 2048, "k_gemm_decode"), (8, 8448, 2048, "k_gemm_decode"), (4, 8704, 4096, "k_gemm_decode"),
     (8, 10240, 2048, "k_gemm_decode"), (9, 7680, 2048, "k_gemm_decode"), (20, 4352, 2048, "k_gemm_decode"),
-    (16, 1024, 3072, "k_gemm_decode"), (58, 1024, 5056, "k_gemm_decode"),
-    # up to 8 tokens from there on 8 x 32, K split (8 x 11008 x 2048: 6.1 / 7.7, streaming 7.8 / 7.9; 1 x 12288 x 2048: 6.3 / 7.6, 7.3 / 7.3;
-    # 5 x 15360 x 1024: 6.8 / 9.0, 9.3 / 9.4; 1 x 22016 x 3072: 9.4 / 12.6, 12.2 / 12.7; 1 x 32768 x 2048: 11.4 / 14.1, 14.4 / 14.5)
-    (8, 11008, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 12288, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"),
-    (2, 12288, 2112, "k_gemm_kslice<8, 32, 8, 3, 0>"), (3, 15360, 1356, "k_gemm_kslice<8, 32, 8, 3, 0>"),
-    (5, 15360, 1024, "k_gemm_kslice<8, 32, 8, 3, 0>"), (2, 15360, 3072, "k_gemm_kslice<8, 32, 8, 3, 0>"),
-    (1, 22016, 3072, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 32768, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"),
-    # 9 .. 16 tokens on 16 x 32 (9 x 8448 x 2048: 5.4 / 6.9, streaming 6.4 / 6.7; 16 x 8448 x 2048: 5.4 / 7.3, 7.2 / 7.6)
-    (9, 8448, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"), (16, 8448, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"),
-    (12, 8704, 4096, "k_gemm_kslice<16, 32, 8, 3, 0>"), (12, 8704, 4160, "k_gemm_kslice<32, 32, 8, 2, 0>"),
-    # from a second round of 4096 channels, or with more tokens, 32 x 32 and larger (1 x 12288 x 5120: 8.1 / 10.0, streaming 13.3 / 13.0;
-    # 32 x 15360 x 4096: 9.0 / 13.4, 18.8 / 19.2)
+    (16, 1024, 3072, "k_gemm_decode"), (58, 1024, 5056, "k_gemm_decode"), (1, 12288, 2048, "k_gemm_decode"), (2, 12288, 2112, "k_gemm_decode"), (2, 14848, 2048, "k_gemm_decode"),
+    (4, 14848, 2048, "k_gemm_decode"), (9, 8448, 2048, "k_gemm_decode"), (10, 8448, 2048, "k_gemm_decode"), (12, 8704, 4096, "k_gemm_decode"), (12, 9984, 2048, "k_gemm_decode"),
+    # beyond these lines 8 x 32 and 16 x 32, K split (8 x 11008 x 2048 7.5 / 7.6 and 6.1 / 7.8, 1 x 15360 x 4096 9.4 / 9.5 and 7.9 / 9.9,
+    # 1 x 22016 x 3072 12.2 / 12.8 and 9.8 / 13.0, 1 x 32768 x 2048 14.3 / 14.4 and 11.8 / 14.4, 8 x 15104 x 2048 9.4 / 9.5 and 7.2 / 9.4,
+    # 5 x 15360 x 1024 9.0 / 9.1 and 6.6 / 9.1, 10 x 15104 x 2048 9.8 / 9.8 and 7.3 / 9.9, 11 x 10240 x 2048 8.1 / 8.2 and 5.8 / 8.4,
+    # 16 x 8448 x 2048 7.1 / 7.3 and 5.2 / 7.4)
+    (8, 11008, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (5, 11008, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 15104, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 15360, 4096, "k_gemm_kslice<8, 32, 8, 3, 0>"), (1, 22016, 3072, "k_gemm_kslice<8, 32, 8, 3, 0>"),
+    (1, 32768, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (2, 15104, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (8, 15104, 2048, "k_gemm_kslice<8, 32, 8, 3, 0>"), (3, 15360, 1356, "k_gemm_kslice<8, 32, 8, 3, 0>"), (5, 15360, 1024, "k_gemm_kslice<8, 32, 8, 3, 0>"), (2, 15360, 3072, "k_gemm_kslice<8, 32, 8, 3, 0>"),
+    (10, 15104, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"), (9, 10240, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"), (11, 10240, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"), (13, 8448, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"), (16, 8448, 2048, "k_gemm_kslice<16, 32, 8, 3, 0>"),
+    (12, 8704, 4160, "k_gemm_kslice<32, 32, 8, 2, 0>"),
+    # from a second round of 4096 channels, or with more tokens, 32 x 32 and larger (1 x 12288 x 5120: 8.3 / 10.0, streaming 12.8 / 12.8;
+    # 12 x 8704 x 4160: 6.4 / 7.9, 11.7 / 11.9; 32 x 15360 x 4096: 9.0 / 13.4, 18.8 / 19.2)
     (1, 12288, 5120, "k_gemm_kslice<32, 32, 8, 2, 0>"), (4, 8704, 6144, "k_gemm_kslice<32, 32, 8, 2, 0>"),
     (32, 15360, 4096, "k_gemm_kslice<32, 32, 8, 2, 0>"), (48, 8704, 6144, "k_gemm_kslice<64, 32, 8, 3, 0>"),
     # small outputs: each K-split tile, and the 64 x 64 tile where K is short or the tiles many

@@ -409,7 +409,8 @@ def test_gemm_k_split_extreme_sums(tile):
 
 # The automatic choice on either side of its lines: few tokens, small outputs, one round of 128 x 128.
 @pytest.mark.parametrize("T,d_e,N,kernel", [
-    (2, 12288, 2112, "k_gemm_kslice<8, 32,"), (8, 8704, 2048, "k_gemm_decode"), (13, 8704, 1999, "k_gemm_kslice<16, 32,"), (1, 12288, 4160, "k_gemm_kslice<32, 32,"), (20, 8704, 1000, "k_gemm_kslice<32, 32,"),
+    (2, 12288, 2112, "k_gemm_decode"), (2, 15360, 2112, "k_gemm_kslice<8, 32,"), (12, 8704, 1999, "k_gemm_decode"), (13, 8704, 1999, "k_gemm_kslice<16, 32,"),
+    (1, 12288, 4160, "k_gemm_kslice<32, 32,"), (20, 8704, 1000, "k_gemm_kslice<32, 32,"),
     (58, 1024, 5056, "k_gemm_decode"), (48, 8704, 6144, "k_gemm_kslice<64, 32,"), (70, 1024, 9000, "k_gemm_mfma<64, 64,"),
     (333, 9728, 1999, "k_gemm_kslice<64, 64,"), (517, 8704, 2048, "k_gemm_kslice<96, 64,"), (700, 8704, 4096, "k_gemm_kslice<128, 128,"),
     (700, 4352, 4000, "k_gemm_mfma<128, 128,")])
