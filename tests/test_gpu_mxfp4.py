@@ -108,7 +108,7 @@ def test_mxfp4_gemm_two_groups_of_tokens_on_few_chunks(T, d_e):
         check_mx_gemm(y, qx, ex, qw, ew)
 
 
-@pytest.mark.parametrize("tile", range(1, 12))
+@pytest.mark.parametrize("tile", range(1, 15))
 def test_mxfp4_gemm_every_tile(tile):
     rng = np.random.default_rng(tile)
     T, N, d_e = 300, 520, 1280
@@ -121,6 +121,21 @@ def test_mxfp4_gemm_every_tile(tile):
     pme.set_gemm_tile(100 + tile)
     y = pme.mxfp4_gemm(*args).to(torch.float32).cpu().numpy()
     check_mx_gemm(y, qx, ex, qw, ew)
+
+
+# Outputs that the automatic choice gives to the tiles of 128 x 64, 192 x 128 and 256 x 192: several tiles in both directions, the last of
+# either ragged.  Rows are sampled so that each of a tile's waves and every token fragment of a wave has some.
+@pytest.mark.parametrize("T,d_e,N,tile", [(267, 12288, 4352, "128, 64"), (2895, 15360, 5457, "192, 128"), (3606, 9728, 3136, "256, 192")])
+def test_mxfp4_gemm_automatic_choice(T, d_e, N, tile):
+    g = torch.Generator(device="cuda").manual_seed(T)
+    qx, qw = (torch.randint(0, 256, (n, d_e // 2), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
+    ex, ew = (torch.randint(118, 130, (n, d_e // 32), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
+    assert pme.gemm_plan(T, d_e, N, variant=2).startswith(f"k_mxgemm_mfma<{tile}, ")
+    pme.set_path(MFMA)
+    y = pme.mxfp4_gemm(qx, ex, qw, ew)
+    rows = torch.unique(torch.cat([torch.arange(7, T, max(29, T // 24 // 32 * 32 + 29)), torch.tensor([0, T - 1])])).cuda()
+    check_mx_gemm(y[rows].float().cpu().numpy(), oracle.unpack_fp4(qx[rows].cpu().numpy()), ex[rows].cpu().numpy(),
+                  oracle.unpack_fp4(qw.cpu().numpy()), ew.cpu().numpy())
 
 
 # Scale bytes arrive in groups of 512 codes: less than one group, whole ones, a remainder of 128 and of 256 codes, and more
