@@ -395,15 +395,16 @@ def test_gemm_k_split_tiles_on_whole_lines(tile, d_e):
         pme.set_gemm_tile(0)
 
 
-@pytest.mark.parametrize("tile", range(29, 35))
-def test_gemm_k_split_extreme_sums(tile):
-    # the largest x256 accumulators that the matrix-core kernels admit: (-8) (-8) at every step of the longest K
-    T, N, d_e = 70, 40, (1 << 17) - 128
+@pytest.mark.parametrize("tile,d_e", [(t, (1 << 17) - 128) for t in range(29, 35)] + [(t, (1 << 17) - 256) for t in range(29, 37)])
+def test_gemm_k_split_extreme_sums(tile, d_e):
+    # the largest x256 accumulators that the matrix-core kernels admit, on half lines and on whole ones (an odd and an even number of
+    # 128 codes): (-8) (-8) at every step of the longest K
+    T, N = 70, 40
     qx = torch.full((T, d_e // 2), 0x88, dtype=torch.uint8, device="cuda")
     qw = torch.full((N, d_e // 2), 0x88, dtype=torch.uint8, device="cuda")
     pme.set_path(MFMA)
     pme.set_gemm_tile(tile)
-    assert pme.gemm_plan(T, d_e, N).startswith("k_gemm_kslice<%d, %d, " % K_SPLIT_TILES[tile - 29])
+    assert pme.gemm_plan(T, d_e, N).startswith("k_gemm_kslice<%d, %d, " % (K_SPLIT_TILES + ((8, 32), (16, 32)))[tile - 29])
     assert bool((pme.w4a4_gemm_i32(qx, qw) == 64 * d_e).all())
 
 
