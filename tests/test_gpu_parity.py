@@ -998,7 +998,7 @@ def test_probe_copy():
 
 # One token through the layer in one kernel: bit for bit what the two kernels give.  Blocks of 64 and of 128 columns (with a folded
 # one), channels around the workgroup's 16 and the limit of 4096, inputs that end inside a base row and in the first row of the
-# last K step of the block, every kind of token the range can meet.
+# last K step of the block, every kind of token the range can meet.  The one kernel leaves the workspace as it was, the two write it.
 @pytest.mark.parametrize("d,d_e", ((8192, 8448), (8184, 8960), (6152, 9728), (8192, 9728), (8192, 8704), (4104, 8704), (8192, 10240)))
 @pytest.mark.parametrize("N", (1, 16, 250, 4096, 4097))
 def test_one_token_layer_equals_the_two_kernels(d, d_e, N):
@@ -1015,9 +1015,13 @@ def test_one_token_layer_equals_the_two_kernels(d, d_e, N):
         x = x.to(torch.bfloat16)
         qx, sx = pme.hadamard_expand_quant(x, d_e)
         guard = torch.full((2, N + 3), 9.0, dtype=torch.bfloat16, device="cuda")
-        y = pme.expanded_linear(x, d_e, qw, sw, guard[:1, :N])
+        ws = torch.full((pme.workspace_bytes(1, d, d_e, N),), 0x5A, dtype=torch.uint8, device="cuda")
+        y = pme.expanded_linear(x, d_e, qw, sw, guard[:1, :N], ws)
+        assert bool((ws == 0x5A).all()) == (N <= 4096)
         assert torch.equal(y.view(torch.int16), pme.w4a4_gemm(qx, sx, qw, sw).view(torch.int16))
         assert bool((guard[0, N:] == 9.0).all()) and bool((guard[1] == 9.0).all())
         qx, sx, zx = pme.hadamard_expand_quant_asym(x, d_e)
-        y = pme.expanded_linear_asym(x, d_e, qw, sw, wsum)
+        ws.fill_(0x5A)
+        y = pme.expanded_linear_asym(x, d_e, qw, sw, wsum, workspace=ws)
+        assert bool((ws == 0x5A).all()) == (N <= 4096)
         assert torch.equal(y.view(torch.int16), pme.w4a4_gemm_asym(qx, sx, zx, qw, sw, wsum).view(torch.int16))
