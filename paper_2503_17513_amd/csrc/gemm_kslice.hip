@@ -11,8 +11,8 @@
 // one), and each wave finishes what it added.
 // What bounds this kernel is the way from L2 into LDS, which takes a line of 128 bytes at a time: a step of 128 codes asks for half
 // lines and gets half the rate.  Where d_e is a multiple of 256 and LDS has room a step is 256 codes, whole lines.  Layers, half
-// and whole lines, us (three sets of operands in turn): 32 x 4096 x 15360 17.9 and 15.0, 517 x 2048 x 8704 25.2 and 22.5, 1673 x 896 x
-// 22016 73.3 and 66.8, 48 x 6144 x 8704 14.9 and 13.9, 463 x 640 x 18432 25.0 and 22.7; 333 x 2048 x 9728 19.0 either way.  Few tokens,
+// and whole lines, us (three sets of operands in turn): 32 x 4096 x 15360 16.7 and 14.1, 517 x 2048 x 8704 24.1 and 22.1, 1673 x 896 x
+// 22016 71.4 and 67.0, 48 x 6144 x 8704 14.2 and 13.1, 463 x 640 x 18432 24.5 and 21.5, 333 x 2048 x 9728 18.1 and 17.3.  Few tokens,
 // weight-streaming kernel and 8 or 16 x 32 of whole lines, GEMM alone, us from the caches / from memory: 8 x 1088 x 22016 12.6 / 12.7 and
 // 8.9 / 11.7, 16 x 2048 x 10240 9.0 / 9.1 and 6.2 / 8.8; but 12 x 2048 x 8704 6.9 / 6.9 and 5.2 / 7.4, which streams (see kslice_cost).
 // Consecutive steps of one wave instead of every NW-th: 2-5 % slower.
@@ -474,9 +474,9 @@ template <int AR, int BN, int NW, int NSTAGE, bool ODD> pme_status launch_kslice
 
 // The caller has checked that d_e % 128 == 0, that d_e is in the accumulator's range and that code rows are 16-byte aligned.
 // Two waves per SIMD where their registers and rings allow (up to 64 x 64): one alone issues a vector instruction only
-// every five cycles and could not unpack as fast as the matrix cores consume (64 x 64, layer 333 x 2048 x 9728: 20.2 us with
-// four waves, 19.0 with eight).  32 x 32 with two steps (one in LDS, one in registers) leaves room for two workgroups per
-// compute unit; 64 x 32 keeps two steps in registers, since a second one does not fit in LDS (112 x 2560 x 15360: 17.9 us, 20.0 on
+// every five cycles and could not unpack as fast as the matrix cores consume (64 x 64, layer 333 x 2048 x 9728: four
+// waves 6 % slower than eight).  32 x 32 with two steps (one in LDS, one in registers) leaves room for two workgroups per
+// compute unit; 64 x 32 keeps two steps in registers, since a second one does not fit in LDS (112 x 2560 x 15360: 16.7 us, 18.8 on
 // half lines).  Measured and not kept: four waves at 32 x 32 and 64 x 32 (up to 7 % slower), four stages at 8 and 16 x 32.
 pme_status launch_gemm_kslice(const GemmArgs& a, int tile) {
     switch (tile) {
@@ -515,6 +515,9 @@ const double kLinesLoader64[8] = {2.993, 0.03986, 0.1686, 0.005481, 0.07819, 0.0
 // turn (in the caches) and with 600 MB of them in turn (from memory); the estimate is of the geometric mean of the two, good
 // to 4-10 % for the K-split tiles and 5 % for the others.  Weights that come from memory slow the K-split kernel most (64-byte
 // rows, a ring of two or three steps: 16 x 2048 x 8704 takes 6.6 us warm and 9.5 cold, the streaming kernel 8.0 and 7.8).
+// The fit is of half lines.  Where d_e is a multiple of 256 the tiles up to 96 x 64 run on whole lines here too, on the same choice: 0.97
+// of the half lines' time from the caches and 0.89 from memory in the mean of 840 outputs of d_e 1024 .. 7936, three of them more than 3 %
+// slower in the geometric mean (largest 5 %), and within 1-2 % of the fastest tile.
 
 // K-split tile: one round of workgroups; the 32 x 32 one, of which two share a compute unit, also several.  A second round of
 // the others pays prologue and sum again and loses to the tiled kernel (647 x 2834 x 9728: 33.5 us on two rounds of 64 x 64, 26.9

@@ -10,8 +10,8 @@
 // layer 333 x 2048 x 9728 21.1 us with 64-byte rows, 18.8 with 128), and the scale bytes of 512 codes at a time, sixteen a row
 // (25.5 us with the four of every 128 codes).  Contiguous K: what a wave fetches next is in the line after, or in the same one.
 // The layer on 64 x 64 tiles whose waves share the K loop, and on this kernel (us, three sets of operands in turn): 46 x 3904 x
-// 22016 45.8 and 26.8, 78 x 704 x 15360 35.0 and 16.0, 265 x 604 x 8960 26.4 and 15.0, 333 x 2048 x 9728 25.0 and 18.8; and on the
-// weight-streaming kernel: 10 x 4864 x 10240 22.8 and 11.7, 16 x 2048 x 8704 12.6 and 10.6.
+// 22016 45.7 and 26.4, 78 x 704 x 15360 35.1 and 14.1, 265 x 604 x 8960 26.1 and 15.5, 333 x 2048 x 9728 24.6 and 18.7; and on the
+// weight-streaming kernel: 10 x 4864 x 10240 22.5 and 11.5, 16 x 2048 x 8704 12.7 and 10.4.
 #include "gemm_tile.h"
 
 #include <algorithm>

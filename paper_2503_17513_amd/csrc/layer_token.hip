@@ -3,8 +3,8 @@
 // One token through two kernels is bound by the host, which takes 3.4 us to enqueue a kernel with arguments (and 10 us for the
 // call), and on the GPU by two chains of latencies with a launch between them (4.6 + 5.3 us).  Here every workgroup rotates the token
 // itself and multiplies it with 16 channels, whose weights it has asked for before the rotation and finds in registers
-// after it; no codes pass through memory.  1 x 2048 x 8448 9.5 -> 7.6 us a call, 1 x 2048 x 8704 9.7 -> 7.9, 1 x 4096 x 8448 9.7 -> 8.1,
-// 1 x 2048 x 10240 10.6 -> 9.0.  A second token costs every workgroup another 1.6 us and gains nothing any more (2 x 2048 x 8448 9.4 and
+// after it; no codes pass through memory.  Us a call in a Python loop / in a graph, three sets of operands in turn: 1 x 2048 x 8448 9.8 / 8.3 ->
+// 7.2 / 6.9, 1 x 2048 x 8704 9.8 / 9.2 -> 8.0 / 7.9, 1 x 4096 x 8448 10.0 / 9.3 -> 8.1 / 8.4, 1 x 2048 x 10240 10.5 / 10.1 -> 8.5 / 8.5.  A second token costs every workgroup another 1.6 us and gains nothing any more (2 x 2048 x 8448 9.4 and
 // 9.2), nor do the blocks of 256 columns, whose token is three to five waves' work (1 x 2048 x 12288 11.2 either way).
 //   1. the token is fetched into LDS by DMA, the wave's block fragments and weights into registers;
 //   2. base block on the matrix cores, butterflies in registers, range across the waves, codes into the token's place in LDS, as
